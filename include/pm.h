@@ -7,11 +7,13 @@
  * where CT_psi is the merged Cooley-Tukey NTT (Alg. 5: normal order in,
  * bit-reversed order out, powers of psi folded into the twiddles), "." is the
  * pointwise product mod q, and GS'_{psi^-1} is the merged Gentleman-Sande NTT
- * (Alg. 6: bit-reversed in, normal out) whose butterflies halve both outputs,
- * which merges the 1/N scaling. Every product is reduced with the paper's
- * Barrett variant (Alg. 4, constant mu = floor(2^(2m+1)/q), m = len(q),
- * at most one correctional subtraction). Arithmetic is exact: every output
- * word is the canonical residue in [0, q).
+ * (Alg. 6: bit-reversed in, normal out) with the 1/N scaling merged. Pointwise
+ * products are reduced with the paper's Barrett variant (Alg. 4, m = len(q));
+ * the transforms' twiddle products use a quotient precomputed from the same
+ * constant and words that are reduced only as far as the word size needs.
+ * Arithmetic is exact: every output word is the canonical residue in [0, q).
+ * pm_barrett_mulmod and pm_polymul_stagewise are Alg. 4 and Eq. 2 as printed
+ * (halved butterflies, at most one correctional subtraction per product).
  *
  * Conventions for every entry point:
  *   - Array pointers marked "device" are caller-owned device memory (e.g.
@@ -82,8 +84,7 @@ int pm_ntt_fwd(uint64_t *x, size_t N, size_t limbs, size_t polys_per_limb, const
                const uint64_t *psi_br, pm_stream_t stream);
 
 /*
- * In-place inverse: merged GS NTT (Alg. 6) with each butterfly output halved
- * (Eq. 2), so the result includes the 1/N factor and pm_ntt_inv(pm_ntt_fwd(x))
+ * In-place inverse: merged GS NTT (Alg. 6) scaled by 1/N (Eq. 2), so the result includes the 1/N factor and pm_ntt_inv(pm_ntt_fwd(x))
  * = x. x: device, bit-reversed in, normal out. psi_inv_br: device [limbs][N].
  */
 int pm_ntt_inv(uint64_t *x, size_t N, size_t limbs, size_t polys_per_limb, const uint64_t *q,
@@ -104,7 +105,7 @@ int pm_polymul(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N, size
  * CT NTTs of a and b (last stage omitted), the last CT stages, the pointwise
  * product and the first GS stage fused into Alg. 7 on adjacent pairs (four
  * products per pair, twiddle alpha^2 = (-1)^i psi_br[N/4 + i/2]), truncated
- * merged GS NTT (first stage omitted) with halved butterflies. Same result,
+ * merged GS NTT (first stage omitted) scaled by 2/N. Same result,
  * arguments and workspace as pm_polymul; N = 2 runs the unfused product.
  */
 int pm_polymul_fused(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N, size_t limbs,

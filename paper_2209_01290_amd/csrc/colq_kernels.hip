@@ -12,8 +12,9 @@
 // t / q and stage s+1 pairs (0,1), (2,3) in groups 2(t / q) and 2(t / q) + 1.
 // When log2 R is odd, stage 0 runs alone in the first forward round (the
 // last inverse round) with q = R/4. The inverse runs the rounds backwards,
-// each round's stages in reverse order, with the halved GS butterflies of
-// Eq. 2. Rounds exchange registers through LDS; the two exchange buffers
+// each round's stages in reverse order. Forward words leave lazy (the row pass
+// reduces them); the inverse takes the row pass's scaled lazy words and leaves
+// canonical ones. Rounds exchange registers through LDS; the two exchange buffers
 // alternate, so one barrier per exchange suffices.
 //
 // grid: x = block of CPW columns, y = poly, z = limb * nops + op;
@@ -64,6 +65,45 @@ __device__ __forceinline__ void colq_exchange(W* buf, W (&x)[4], uint32_t t, uin
   for (int k = 0; k < 4; ++k) x[k] = buf[(colq_row<LQ_TO>(t, k) << logcpw) + j];
 }
 
+// Round RHO and those after it, forward: the round's one or two stages on words
+// below B, then the exchange to the next round's layout.
+template <int LOGR, int KIND, int RHO, int B, int NT, typename W, typename MT>
+__device__ __forceinline__ void colq_fwd(W* buf, W* other, W (&x)[4], const W (&ta)[NT], const W (&tb)[NT],
+                                         const W (&tc)[NT], uint32_t t, uint32_t j, uint32_t logcpw, const MT& M) {
+  using G = ColqGeom<LOGR>;
+  constexpr CtStage s0 = ct_stage<W, KIND>(B, false), s1 = ct_stage<W, KIND>(s0.out, false);
+  const Tw<W> a = tw_vec<KIND>(ta[RHO], M);
+  ct_lazy<KIND>(x[0], x[2], a, s0.red, s0.k, M);
+  ct_lazy<KIND>(x[1], x[3], a, s0.red, s0.k, M);
+  if constexpr (G::len(RHO) == 2) {
+    ct_lazy<KIND>(x[0], x[1], tw_vec<KIND>(tb[RHO], M), s1.red, s1.k, M);
+    ct_lazy<KIND>(x[2], x[3], tw_vec<KIND>(tc[RHO], M), s1.red, s1.k, M);
+  }
+  if constexpr (RHO + 1 < G::NRND) {
+    colq_exchange<G::lq(RHO), G::lq(RHO + 1)>(buf, x, t, j, logcpw);
+    colq_fwd<LOGR, KIND, RHO + 1, (G::len(RHO) == 2 ? s1.out : s0.out)>(other, buf, x, ta, tb, tc, t, j, logcpw, M);
+  }
+}
+
+// Round RHO and those before it, inverse, on words below GIN.
+template <int LOGR, int KIND, int RHO, int NT, typename W, typename MT>
+__device__ __forceinline__ void colq_inv(W* buf, W* other, W (&x)[4], const W (&ta)[NT], const W (&tb)[NT],
+                                         const W (&tc)[NT], uint32_t t, uint32_t j, uint32_t logcpw, const MT& M) {
+  using G = ColqGeom<LOGR>;
+  GsBounds<W, KIND, 4> B(LazyRule<W, KIND>::GIN);
+  if constexpr (G::len(RHO) == 2) {
+    gs_track<KIND>(x, B, 0, 1, tw_vec<KIND>(tb[RHO], M), false, M);
+    gs_track<KIND>(x, B, 2, 3, tw_vec<KIND>(tc[RHO], M), false, M);
+  }
+  const Tw<W> a = tw_vec<KIND>(ta[RHO], M);
+  gs_track<KIND>(x, B, 0, 2, a, false, M);
+  gs_track<KIND>(x, B, 1, 3, a, false, M);
+  if constexpr (RHO > 0) {
+    colq_exchange<G::lq(RHO), G::lq(RHO - 1)>(buf, x, t, j, logcpw);
+    colq_inv<LOGR, KIND, RHO - 1>(other, buf, x, ta, tb, tc, t, j, logcpw, M);
+  }
+}
+
 template <int LOGR, int KIND, int INV, typename W>
 __global__ void __launch_bounds__(COLQ_WG)
 k_colq(const W* src0, W* dst0, const W* src1, W* dst1, const W* __restrict__ tw, uint32_t log2n, uint32_t polys,
@@ -97,33 +137,7 @@ k_colq(const W* src0, W* dst0, const W* src1, W* dst1, const W* __restrict__ tw,
     constexpr int LQ0 = G::lq(0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = src[(size_t)colq_row<LQ0>(t, k) * C];
-    ct_bfly<KIND>(x[0], x[2], ta[0], M);
-    ct_bfly<KIND>(x[1], x[3], ta[0], M);
-    if (G::len(0) == 2) {
-      ct_bfly<KIND>(x[0], x[1], tb[0], M);
-      ct_bfly<KIND>(x[2], x[3], tc[0], M);
-    }
-    if constexpr (G::NRND > 1) {
-      colq_exchange<G::lq(0), G::lq(1)>(lds[0], x, t, j, logcpw);
-      ct_bfly<KIND>(x[0], x[2], ta[1], M);
-      ct_bfly<KIND>(x[1], x[3], ta[1], M);
-      ct_bfly<KIND>(x[0], x[1], tb[1], M);
-      ct_bfly<KIND>(x[2], x[3], tc[1], M);
-    }
-    if constexpr (G::NRND > 2) {
-      colq_exchange<G::lq(1), G::lq(2)>(lds[1], x, t, j, logcpw);
-      ct_bfly<KIND>(x[0], x[2], ta[2], M);
-      ct_bfly<KIND>(x[1], x[3], ta[2], M);
-      ct_bfly<KIND>(x[0], x[1], tb[2], M);
-      ct_bfly<KIND>(x[2], x[3], tc[2], M);
-    }
-    if constexpr (G::NRND > 3) {
-      colq_exchange<G::lq(2), G::lq(3)>(lds[0], x, t, j, logcpw);
-      ct_bfly<KIND>(x[0], x[2], ta[3], M);
-      ct_bfly<KIND>(x[1], x[3], ta[3], M);
-      ct_bfly<KIND>(x[0], x[1], tb[3], M);
-      ct_bfly<KIND>(x[2], x[3], tc[3], M);
-    }
+    colq_fwd<LOGR, KIND, 0, Q1>(lds[0], lds[1], x, ta, tb, tc, t, j, logcpw, M);
     constexpr int LQL = G::lq(G::NRND - 1);
 #pragma unroll
     for (int k = 0; k < 4; ++k) dst[(size_t)colq_row<LQL>(t, k) * C] = x[k];
@@ -131,33 +145,8 @@ k_colq(const W* src0, W* dst0, const W* src1, W* dst1, const W* __restrict__ tw,
     constexpr int LQL = G::lq(G::NRND - 1);
 #pragma unroll
     for (int k = 0; k < 4; ++k) x[k] = src[(size_t)colq_row<LQL>(t, k) * C];
-    if constexpr (G::NRND > 3) {
-      gs_bfly_half<KIND>(x[0], x[1], tb[3], M);
-      gs_bfly_half<KIND>(x[2], x[3], tc[3], M);
-      gs_bfly_half<KIND>(x[0], x[2], ta[3], M);
-      gs_bfly_half<KIND>(x[1], x[3], ta[3], M);
-      colq_exchange<G::lq(3), G::lq(2)>(lds[0], x, t, j, logcpw);
-    }
-    if constexpr (G::NRND > 2) {
-      gs_bfly_half<KIND>(x[0], x[1], tb[2], M);
-      gs_bfly_half<KIND>(x[2], x[3], tc[2], M);
-      gs_bfly_half<KIND>(x[0], x[2], ta[2], M);
-      gs_bfly_half<KIND>(x[1], x[3], ta[2], M);
-      colq_exchange<G::lq(2), G::lq(1)>(lds[1], x, t, j, logcpw);
-    }
-    if constexpr (G::NRND > 1) {
-      gs_bfly_half<KIND>(x[0], x[1], tb[1], M);
-      gs_bfly_half<KIND>(x[2], x[3], tc[1], M);
-      gs_bfly_half<KIND>(x[0], x[2], ta[1], M);
-      gs_bfly_half<KIND>(x[1], x[3], ta[1], M);
-      colq_exchange<G::lq(1), G::lq(0)>(lds[0], x, t, j, logcpw);
-    }
-    if (G::len(0) == 2) {
-      gs_bfly_half<KIND>(x[0], x[1], tb[0], M);
-      gs_bfly_half<KIND>(x[2], x[3], tc[0], M);
-    }
-    gs_bfly_half<KIND>(x[0], x[2], ta[0], M);
-    gs_bfly_half<KIND>(x[1], x[3], ta[0], M);
+    colq_inv<LOGR, KIND, G::NRND - 1>(lds[0], lds[1], x, ta, tb, tc, t, j, logcpw, M);
+    canon_all<KIND>(x, M);
     constexpr int LQ0 = G::lq(0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) dst[(size_t)colq_row<LQ0>(t, k) * C] = x[k];

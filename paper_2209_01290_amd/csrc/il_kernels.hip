@@ -9,8 +9,12 @@
 // sequence of such passes over HBM. A block of stages s0..s0+LOGR-1 is one
 // grid row (blockIdx.y), so its twiddles are uniform across the workgroup.
 //
+// Words between the passes of one transform are lazy (below LazyRule's H on the
+// way forward, below GIN on the way back); the last pass makes them canonical,
+// and the inverse's last stage scales by 1/N.
+//
 //   IL_FWD  stages of Alg. 5 on one or two operands (A -> C, B -> D)
-//   IL_INV  stages of Alg. 6 with halved butterflies (A -> C)
+//   IL_INV  stages of Alg. 6 (A -> C)
 //   IL_MUL  the last block of Alg. 5 on A and on B, the pointwise product and
 //           the first block of Alg. 6 (A, B -> C): Eq. 2's middle, fused
 #include <hip/hip_runtime.h>
@@ -28,6 +32,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(IlWave
 k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint64_t* __restrict__ twf,
      const uint64_t* __restrict__ twi, uint32_t log2n, uint32_t s0, uint32_t polys, uint32_t nops, LimbSet ls) {
   constexpr int R = 1 << LOGR;
+  using L = LazyRule<uint64_t, KIND>;
+  constexpr int H = L::H;
   const uint32_t p0 = blockIdx.x * blockDim.x;    // first polynomial of the workgroup
   const uint32_t lane = threadIdx.x;
   if (p0 + lane >= polys) return;
@@ -48,7 +54,8 @@ k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint6
     uint64_t* dst = (op ? D : C) + base;
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (src + i * step)[lane];
-    blk_fwd<LOGR, KIND>(x, twf + (size_t)limb * N, rb, M);
+    blk_fwd<LOGR, KIND, true, H>(x, twf + (size_t)limb * N, rb, M);
+    if (s0 + LOGR == log2n) canon_all<KIND>(x, M);      // the transform's last block
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   } else if constexpr (MODE == IL_INV) {
@@ -56,7 +63,8 @@ k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint6
     uint64_t* dst = C + base;
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (src + i * step)[lane];
-    blk_inv<LOGR, KIND>(x, twi + (size_t)limb * N, rb, M);
+    blk_inv<LOGR, KIND, true, L::GIN>(x, twi + (size_t)limb * N, rb, s0 == 0, log2n, M);
+    if (s0 == 0) canon_all<KIND>(x, M);
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   } else {
@@ -66,14 +74,15 @@ k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint6
     uint64_t* dst = C + base;
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (sa + i * step)[lane];
-    blk_fwd<LOGR, KIND>(x, tf, rb, M);
+    blk_fwd<LOGR, KIND, true, H>(x, tf, rb, M);
     uint64_t y[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) y[i] = (sb + i * step)[lane];
-    blk_fwd<LOGR, KIND>(y, tf, rb, M);
+    blk_fwd<LOGR, KIND, true, H>(y, tf, rb, M);
 #pragma unroll
-    for (int i = 0; i < R; ++i) x[i] = mulmod<KIND>(x[i], y[i], M);
-    blk_inv<LOGR, KIND>(x, twi + (size_t)limb * N, rb, M);
+    for (int i = 0; i < R; ++i) x[i] = mul_lazy<KIND>(x[i], y[i], M);
+    blk_inv<LOGR, KIND, true, L::PW>(x, twi + (size_t)limb * N, rb, s0 == 0, log2n, M);
+    if (s0 == 0) canon_all<KIND>(x, M);
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   }

@@ -1,0 +1,317 @@
+// Lazily reduced modular arithmetic of the transforms' butterflies, on both
+// word types. The butterflies work on representatives that may exceed q: a
+// word stands for its residue and is only known to be below B q for a bound B
+// that the code tracks at compile time. Canonical words come back at the end
+// of a transform (canon), so results are the same words as with a full
+// reduction in every butterfly.
+//
+// Twiddle products use a precomputed quotient (Shoup's method): for a twiddle
+// w with companion p ~ w 2^64 / q, k = hi64(v p) is v w / q up to a small
+// deficit, and v w - k q needs the low 64 bits of both products only. Alg. 4
+// costs 22 VALU instructions a product, this 11, and the product accumulates
+// onto u, so u + v w costs no addition. The caller's tables hold w alone; p is
+// computed in the kernel from the modulus' Barrett constant: on the scalar
+// unit where the twiddle is uniform over the workgroup (tw_uni), else in
+// the lanes (tw_vec, 6 instructions, once for all butterflies that share the
+// twiddle).
+//
+// The quotient drops what does not fit the cheap instruction sequence, so it
+// may fall short of v w / q. With d the companion's deficit, for v < V q
+//   v w - k q < (3 + d V / H) q,   H q <= 2^64 the headroom,
+// three for the dropped fractions of the 64 x 64 high product (two cross
+// products rounded down one by one, the low product left out).
+//
+// What bounds it: the transforms' rows are bound by VALU issue (97 % of the
+// rate their instruction mix allows), so time follows the instruction count
+// weighted by issue rate: 14 instructions for a CT butterfly and 15 for a GS one
+// plus about 1.3 to 2 for reductions, against 32 and 40.8 with Alg. 4 and full
+// reductions in every butterfly. The product rows of N = 2^16 x 384 (6144 rows
+// of 2^12 words) went from 0.447 to 0.30 ms, 11,116 to 6,300 VALU instructions
+// a thread.
+//
+// Two rules per word type (LazyRule<W, KIND>); bounds are in sixteenths of q:
+//   64-bit, KIND_WIDE (34 <= len(q) <= 60): H = 16; words may grow over several
+//     stages before one operand is reduced (red2).
+//   64-bit KIND_ANY (any len(q) <= 62) and 32-bit words (len(q) <= 30): H = 4,
+//     quotients exact up to one, products < 2 q (Harvey's butterflies), one
+//     conditional subtraction a stage.
+#pragma once
+#include "modarith.hpp"
+#include "modarith32.hpp"
+
+namespace pm {
+
+constexpr int Q1 = 16;                       // one q in bound units
+
+template <typename W, int KIND>
+struct LazyRule {                            // H = 4
+  static constexpr int H = 4 * Q1;
+  static constexpr int GIN = 2 * Q1;         // bound on the words between two inverse rounds
+  static constexpr int PW = 2 * Q1;          // bound on pointwise products
+  static constexpr int rmax(int, bool) { return 2 * Q1; }
+};
+template <>
+struct LazyRule<uint64_t, KIND_WIDE> {
+  static constexpr int H = 16 * Q1;
+  static constexpr int GIN = 8 * Q1;
+  static constexpr int PW = 72;
+  // bound on a twiddle product of a word below v: companion deficit < 2
+  // (tw_uni) or < 4 (tw_vec)
+  static constexpr int rmax(int v, bool uni) { return 3 * Q1 + ((uni ? 2 : 4) * v + 15) / 16; }
+};
+constexpr int ceil_q(int b) { return (b + Q1 - 1) / Q1; }
+
+// A twiddle and its companion.
+template <typename W>
+struct Tw { W w, p; };
+
+// Scalar values the compiler must take as they are: a 64-bit subtraction or a
+// zero-extension it would rebuild from their definition costs more than the
+// multiply-add written here.
+__device__ __forceinline__ uint32_t opaque_s(uint32_t x) { asm("" : "+s"(x)); return x; }
+__device__ __forceinline__ uint64_t opaque_s(uint64_t x) { asm("" : "+s"(x)); return x; }
+__device__ __forceinline__ uint64_t neg_q(const Mod& M) { return opaque_s(0 - M.q); }
+// k q for a small constant k
+template <typename W, typename MT>
+__device__ __forceinline__ W mult_q(int k, const MT& M) { return opaque_s((W)((W)k * M.q)); }
+
+// x + (h << 32), as one addition to the high word
+__device__ __forceinline__ uint64_t add_high(uint64_t x, uint32_t h) {
+  asm("" : "+v"(h));
+  h += hi32(x);
+  asm("" : "+v"(h));
+  return pack64(lo32(x), h);
+}
+
+__device__ __forceinline__ int len_q(const Mod& M) { return 64 - __builtin_clzll(M.q); }
+
+// ------------------------------------------------------------ 64-bit words --
+// hi64(a b) up to a deficit < 3. The last term is added as a multiply by one,
+// which needs no zero-extended register pair.
+__device__ __forceinline__ uint64_t mulhi_low3(uint64_t a, uint64_t b) {
+  const uint64_t x = (uint64_t)hi32(a) * hi32(b) + __umulhi(lo32(a), hi32(b));
+  return (uint64_t)__umulhi(hi32(a), lo32(b)) * opaque_s(1u) + x;
+}
+
+// hi64(a b), exact.
+__device__ __forceinline__ uint64_t mulhi_exact(uint64_t a, uint64_t b) {
+  const uint64_t e = (uint64_t)lo32(a) * hi32(b) + __umulhi(lo32(a), lo32(b));
+  const uint64_t f = (uint64_t)hi32(a) * lo32(b) + lo32(e);
+  return (uint64_t)hi32(a) * hi32(b) + hi32(e) + hi32(f);
+}
+
+// a.b + c.d + e.f + g.h modulo 2^32 as four multiply-adds (the compiler would
+// narrow them to three multiplies and two additions more). w: the words of a
+// twiddle, in scalar registers if UNI.
+template <bool UNI>
+__device__ __forceinline__ uint32_t cross4(uint64_t v, uint64_t w, uint64_t k, uint64_t nq) {
+  uint64_t x, cc;
+  if (UNI)
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0\n\tv_mad_u64_u32 %0, %1, %4, %5, %0\n\t"
+        "v_mad_u64_u32 %0, %1, %6, %7, %0\n\tv_mad_u64_u32 %0, %1, %8, %9, %0"
+        : "=&v"(x), "=&s"(cc)
+        : "v"(lo32(v)), "s"(hi32(w)), "v"(hi32(v)), "s"(lo32(w)), "v"(lo32(k)), "s"(hi32(nq)), "v"(hi32(k)),
+          "s"(lo32(nq)));
+  else
+    asm("v_mad_u64_u32 %0, %1, %2, %3, 0\n\tv_mad_u64_u32 %0, %1, %4, %5, %0\n\t"
+        "v_mad_u64_u32 %0, %1, %6, %7, %0\n\tv_mad_u64_u32 %0, %1, %8, %9, %0"
+        : "=&v"(x), "=&s"(cc)
+        : "v"(lo32(v)), "v"(hi32(w)), "v"(hi32(v)), "v"(lo32(w)), "v"(lo32(k)), "s"(hi32(nq)), "v"(hi32(k)),
+          "s"(lo32(nq)));
+  return lo32(x);
+}
+
+// acc + v w - k q modulo 2^64
+template <bool UNI>
+__device__ __forceinline__ uint64_t fma_q(uint64_t v, uint64_t w, uint64_t k, uint64_t acc, const Mod& M) {
+  const uint64_t nq = neg_q(M);
+  uint64_t s = (uint64_t)lo32(v) * lo32(w) + acc;
+  s = (uint64_t)lo32(k) * lo32(nq) + s;
+  return add_high(s, cross4<UNI>(v, w, k, nq));
+}
+
+// Companions. With ws = w 2^(64-m) and 2^(m+64)/q = 2^64 + M.ml (+ fraction):
+// w 2^64/q = ws + ws M.ml / 2^64. tw_uni: deficit < 2; tw_vec: < 4 for
+// KIND_WIDE. KIND_ANY: the exact floor in both (one correction).
+template <int KIND>
+__device__ __forceinline__ uint64_t companion(uint64_t w, bool uni, const Mod& M) {
+  const uint64_t ws = w << (64 - len_q(M));
+  if (KIND == KIND_WIDE) return ws + (uni ? mulhi_exact(ws, M.ml) : mulhi_low3(ws, M.ml));
+  const uint64_t p = ws + mulhi_exact(ws, M.ml);
+  return p + ((0 - p * M.q) >= M.q ? 1 : 0);      // remainder w 2^64 - p q < 2q
+}
+
+// acc + v t.w mod q: the product is below rmax(V) for v < V q.
+template <int KIND, bool UNI = false>
+__device__ __forceinline__ uint64_t mul_tw(uint64_t v, const Tw<uint64_t>& t, uint64_t acc, const Mod& M) {
+  const uint64_t k = KIND == KIND_WIDE ? mulhi_low3(v, t.p) : mulhi_exact(v, t.p);
+  return fma_q<UNI>(v, t.w, k, acc, M);
+}
+
+// x < H q -> below 2q. KIND_WIDE: k = hi32(x1 c) with x1 = x >> 32 and
+// c = floor(2^64/q) = 2^64/q - f: x/q - k < x0/q + f x1/2^32 + 1 < 2, since
+// f x1/2^32 < f 16q/2^64 <= 16/17 for len(q) = 60 and x0/q < 1/2 for len(q) = 34
+// (each is below 2^-20 where the other is not small).
+template <int KIND>
+__device__ __forceinline__ uint64_t red2(uint64_t x, const Mod& M) {
+  if (KIND != KIND_WIDE) return csub(x, 2 * M.q);
+  const int m = len_q(M);
+  const uint32_t c = (uint32_t)(((uint64_t)1 << (64 - m)) | (M.ml >> m));
+  const uint64_t nq = neg_q(M);
+  const uint32_t k = __umulhi(hi32(x), opaque_s(c));
+  return add_high((uint64_t)k * lo32(nq) + x, k * hi32(nq));
+}
+
+// x < 2q -> canonical; x < H q -> canonical.
+__device__ __forceinline__ uint64_t csub1(uint64_t x, const Mod& M) { return csub(x, M.q); }
+template <int KIND>
+__device__ __forceinline__ uint64_t canon(uint64_t x, const Mod& M) { return csub1(red2<KIND>(x, M), M); }
+
+// Pointwise product of lazy words: Alg. 4's quotient without its correction.
+// Operands are brought below 2q first; the product is below PW.
+//   x < 4 q^2 < 2^(2m+2), c = x >> (m-2) < 2^(m+4) <= 2^64, mu = floor(2^(m+62)/q):
+//   c mu / 2^64 falls short of x/q by less than 1/2 (bits below c) + 1 (mu),
+//   mulhi_low3 by less than 3: r < 4.5 q.
+template <int KIND>
+__device__ __forceinline__ uint64_t mul_lazy2(uint64_t a, uint64_t b, const Mod& M) {   // operands < 2q
+  const uint32_t a0 = lo32(a), a1 = hi32(a), b0 = lo32(b), b1 = hi32(b);
+  const uint64_t P00 = (uint64_t)a0 * b0;
+  const uint64_t mid = (uint64_t)a1 * b0 + (uint64_t)a0 * b1;
+  const uint64_t P11 = (uint64_t)a1 * b1;
+  unsigned cy1, cy2;
+  const uint32_t x0 = lo32(P00);
+  const uint32_t x1 = __builtin_addc(hi32(P00), lo32(mid), 0u, &cy1);
+  const uint32_t x2 = __builtin_addc(lo32(P11), hi32(mid), cy1, &cy2);
+  const uint32_t x3 = hi32(P11) + cy2;
+  const uint64_t c = pack64(__builtin_amdgcn_alignbit(x2, x1, M.s1), __builtin_amdgcn_alignbit(x3, x2, M.s1));
+  const uint64_t k = mulhi_low3(c, ((uint64_t)1 << 62) | (M.ml >> 2));
+  const uint64_t nq = neg_q(M);
+  return add_high((uint64_t)lo32(k) * lo32(nq) + pack64(x0, x1), lo32(k) * hi32(nq) + hi32(k) * lo32(nq));
+}
+
+template <int KIND>
+__device__ __forceinline__ uint64_t mul_lazy(uint64_t a, uint64_t b, const Mod& M) {
+  if (KIND == KIND_WIDE) return mul_lazy2<KIND>(red2<KIND>(a, M), red2<KIND>(b, M), M);
+  return mulmod<KIND>(canon<KIND>(a, M), canon<KIND>(b, M), M);
+}
+
+// ------------------------------------------------------------ 32-bit words --
+// Companion of ws = w 2^(32-m), 2^(m+32)/q = 2^32 + M.ml: deficit < 2. The
+// product of v < 4q is below 2q: its quotient's deficit is 1 + d v/2^32 <= 2,
+// for len(q) <= 29 (v < 2^31) as it is, for len(q) = 30 with the exact floor.
+template <int KIND>
+__device__ __forceinline__ uint32_t companion(uint32_t w, bool, const Mod32& M) {
+  const uint32_t ws = w << (30 - M.s);           // s = m - 2
+  const uint32_t p = ws + __umulhi(ws, M.ml);
+  if (KIND == KIND_WIDE) return p;
+  return p + ((0u - p * M.q) >= M.q ? 1u : 0u);
+}
+
+template <int KIND, bool UNI = false>
+__device__ __forceinline__ uint32_t mul_tw(uint32_t v, const Tw<uint32_t>& t, uint32_t acc, const Mod32& M) {
+  return acc + v * t.w - __umulhi(v, t.p) * M.q;
+}
+
+template <int KIND>
+__device__ __forceinline__ uint32_t red2(uint32_t x, const Mod32& M) { return min(x, x - 2 * M.q); }
+
+__device__ __forceinline__ uint32_t csub1(uint32_t x, const Mod32& M) { return min(x, x - M.q); }
+template <int KIND>
+__device__ __forceinline__ uint32_t canon(uint32_t x, const Mod32& M) { return csub1(red2<KIND>(x, M), M); }
+
+template <int KIND>
+__device__ __forceinline__ uint32_t mul_lazy(uint32_t a, uint32_t b, const Mod32& M) {
+  return mulmod<KIND>(canon<KIND>(a, M), canon<KIND>(b, M), M);
+}
+
+// -------------------------------------------------------------- butterflies --
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ Tw<W> tw_vec(W w, const MT& M) { return {w, companion<KIND>(w, false, M)}; }
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ Tw<W> tw_uni(W w, const MT& M) { return {w, companion<KIND>(w, true, M)}; }
+template <int KIND, bool UNI, typename W, typename MT>
+__device__ __forceinline__ Tw<W> tw_make(W w, const MT& M) { return UNI ? tw_uni<KIND>(w, M) : tw_vec<KIND>(w, M); }
+
+// One CT stage on words below b: the product is below r; u is reduced first
+// when b + K q would exceed the headroom (K q >= r keeps the difference >= 0).
+struct CtStage { bool red; int k, out; };
+template <typename W, int KIND>
+constexpr CtStage ct_stage(int b, bool uni) {
+  using L = LazyRule<W, KIND>;
+  const int k = ceil_q(L::rmax(b, uni));
+  const bool red = b + k * Q1 > L::H;
+  return {red, k, (red ? 2 * Q1 : b) + k * Q1};
+}
+template <typename W, int KIND>
+constexpr int ct_bound(int b, int stages, bool uni) {
+  for (int i = 0; i < stages; ++i) b = ct_stage<W, KIND>(b, uni).out;
+  return b;
+}
+
+// (u, v) -> (u + w v, u - w v + K q)
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ void ct_lazy(W& u, W& v, const Tw<W>& t, bool red, int k, const MT& M) {
+  if (red) u = red2<KIND>(u, M);
+  const W s = mul_tw<KIND>(v, t, u, M);
+  v = ((u << 1) + mult_q<W>(k, M)) - s;
+  u = s;
+}
+
+// (u, v) -> (u + v, w (u - v + K q)), v below K q
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ void gs_lazy(W& u, W& v, const Tw<W>& t, int k, const MT& M) {
+  const W d = u + mult_q<W>(k, M) - v;
+  u = u + v;
+  v = mul_tw<KIND>(d, t, (W)0, M);
+}
+
+// The last GS stage of a transform with the scaling by N^-1 folded in:
+// (u, v) -> (c (u + v), c w (u - v)); c = 1/N, cw = w/N.
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ void gs_lazy_scaled(W& u, W& v, const Tw<W>& c, const Tw<W>& cw, int k, const MT& M) {
+  const W d = u + mult_q<W>(k, M) - v;
+  u = mul_tw<KIND>((W)(u + v), c, (W)0, M);
+  v = mul_tw<KIND>(d, cw, (W)0, M);
+}
+
+// 2^-lg mod q for 2^lg | q - 1
+template <typename W, typename MT>
+__device__ __forceinline__ W inv_pow2(uint32_t lg, const MT& M) { return (W)(M.q - ((M.q - 1) >> lg)); }
+
+// Bounds of E words through inverse stages, kept in a local array whose values
+// fold to constants in the unrolled code.
+template <typename W, int KIND, int E>
+struct GsBounds {
+  int b[E];
+  __device__ __forceinline__ explicit GsBounds(int in) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) b[j] = in;
+  }
+};
+
+// Butterfly of registers i and j (stage twiddle t) with the bounds' upkeep:
+// a sum above half the headroom is reduced (unless keep), so that the next
+// stage's sum and difference fit.
+template <int KIND, int E, typename W, typename MT>
+__device__ __forceinline__ void gs_track(W (&x)[E], GsBounds<W, KIND, E>& B, int i, int j, const Tw<W>& t, bool uni,
+                                         const MT& M) {
+  using L = LazyRule<W, KIND>;
+  const int k = ceil_q(B.b[j]), s = B.b[i] + B.b[j], d = B.b[i] + k * Q1;
+  gs_lazy<KIND>(x[i], x[j], t, k, M);
+  B.b[j] = L::rmax(d, uni);
+  if (s > L::H / 2) {
+    x[i] = red2<KIND>(x[i], M);
+    B.b[i] = 2 * Q1;
+  } else {
+    B.b[i] = s;
+  }
+}
+
+// Canonical words from words below H q.
+template <int KIND, int E, typename W, typename MT>
+__device__ __forceinline__ void canon_all(W (&x)[E], const MT& M) {
+#pragma unroll
+  for (int j = 0; j < E; ++j) x[j] = canon<KIND>(x[j], M);
+}
+
+}  // namespace pm

@@ -1,5 +1,9 @@
 // Word-level modular arithmetic on 64-bit words for gfx950 (CDNA4).
 //
+// The canonical arithmetic: the elementwise product (pm_barrett_mulmod), the
+// per-stage path and the exact form of the pointwise product. The transforms'
+// butterflies use the lazily reduced forms of lazymod.hpp.
+//
 // Every routine takes canonical operands in [0, q) and returns a canonical
 // result; q is odd with bit length m = len(q) <= 62. 64-bit products are
 // assembled from 32x32->64 multiplies (v_mad_u64_u32, v_mul_hi_u32); the VALU
@@ -9,7 +13,8 @@
 //   addmod   modular addition with one correctional subtraction (Alg. 1)
 //   submod   a - b, plus q on borrow (the difference of the GS butterfly)
 //   halfmod  x/2 mod q = (x >> 1) + (x & 1) * ((q + 1) >> 1); it merges the
-//            1/N scaling into the GS butterflies (Sec. III-A, Eq. 2)
+//            1/N scaling into the per-stage path's GS butterflies (Sec. III-A,
+//            Eq. 2)
 //   mulmod   a*b mod q by the proposed Barrett reduction (Alg. 4):
 //            m = len(q), mu = floor(2^(2m+1) / q), c = x >> (m-2),
 //            quot = (c*mu) >> (m+3), r = x - quot*q, at most one r -= q.
@@ -43,7 +48,7 @@ namespace pm {
 struct Mod {
   uint64_t q;      // odd modulus, len(q) = m <= 62
   uint64_t mu;     // mu' as described above
-  uint64_t half;   // (q + 1) / 2
+  uint64_t ml;     // floor(2^(m+64) / q) - 2^64, for the twiddles' companions (lazymod.hpp)
   uint32_t s1;     // funnel shift for c: m-34 if m >= 34, else m-2
   uint16_t wide;   // 1 if the c window is words 1..3 (m >= 34)
   uint16_t t;      // extra right shift of hi64(c*mu'): 1 if m == 62
@@ -146,32 +151,9 @@ template <int KIND>
 __device__ __forceinline__ void gs_bfly_half(uint64_t& u, uint64_t& v, uint64_t xi, const Mod& M) {
   const uint64_t s = addmod(u, v, M.q);
   const uint64_t d = submod(u, v, M.q);
-  u = halfmod(s, M.half);
-  v = mulmod<KIND>(halfmod(d, M.half), xi, M);
-}
-
-// xi/2 mod q, for gs_bfly_htw.
-__device__ __forceinline__ uint64_t half_tw(uint64_t xi, const Mod& M) { return halfmod(xi, M.half); }
-
-// gs_bfly_half with the twiddle halved beforehand (xh = xi/2 mod q):
-// (u, v) -> ((u+v)/2, (u-v) xh); in Z_q, (u-v) xh = xi (u-v)/2. Where one
-// twiddle serves several butterflies, its halving is paid once instead of
-// once per butterfly.
-template <int KIND>
-__device__ __forceinline__ void gs_bfly_htw(uint64_t& u, uint64_t& v, uint64_t xh, const Mod& M) {
-  const uint64_t s = addmod(u, v, M.q);
-  const uint64_t d = submod(u, v, M.q);
-  u = halfmod(s, M.half);
-  v = mulmod<KIND>(d, xh, M);
-}
-
-// Unhalved GS butterfly (Alg. 6 as printed): (u, v) -> (u+v, xi*(u-v)).
-template <int KIND>
-__device__ __forceinline__ void gs_bfly(uint64_t& u, uint64_t& v, uint64_t xi, const Mod& M) {
-  const uint64_t s = addmod(u, v, M.q);
-  const uint64_t d = submod(u, v, M.q);
-  u = s;
-  v = mulmod<KIND>(d, xi, M);
+  const uint64_t half = (M.q >> 1) + 1;          // (q + 1) / 2
+  u = halfmod(s, half);
+  v = mulmod<KIND>(halfmod(d, half), xi, M);
 }
 
 }  // namespace pm

@@ -17,7 +17,7 @@ namespace pm {
 struct Mod32 {
   uint32_t q;      // odd modulus, len(q) = m <= 30
   uint32_t mu;     // mu' as above
-  uint32_t half;   // (q + 1) / 2
+  uint32_t ml;     // floor(2^(m+32) / q) - 2^32, for the twiddles' companions (lazymod.hpp)
   uint32_t s;      // m - 2
   uint32_t t;      // 1 if m == 30, else 0
   uint32_t pad;
@@ -34,10 +34,6 @@ __device__ __forceinline__ uint32_t submod(uint32_t a, uint32_t b, uint32_t q) {
   return min(d, d + q);
 }
 
-__device__ __forceinline__ uint32_t halfmod(uint32_t x, uint32_t half) {
-  return (x >> 1) + ((x & 1) ? half : 0u);
-}
-
 template <int KIND>
 __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, const Mod32& M) {
   const uint64_t x = (uint64_t)a * b;
@@ -46,35 +42,6 @@ __device__ __forceinline__ uint32_t mulmod(uint32_t a, uint32_t b, const Mod32& 
   if (KIND != 0) quot >>= M.t;         // KIND_WIDE (0): every modulus has m <= 29
   const uint32_t r = (uint32_t)x - quot * M.q;
   return min(r, r - M.q);
-}
-
-template <int KIND>
-__device__ __forceinline__ void ct_bfly(uint32_t& u, uint32_t& v, uint32_t xi, const Mod32& M) {
-  const uint32_t w = mulmod<KIND>(v, xi, M);
-  const uint32_t s = addmod(u, w, M.q);
-  v = submod(u, w, M.q);
-  u = s;
-}
-
-template <int KIND>
-__device__ __forceinline__ void gs_bfly_half(uint32_t& u, uint32_t& v, uint32_t xi, const Mod32& M) {
-  const uint32_t s = addmod(u, v, M.q);
-  const uint32_t d = submod(u, v, M.q);
-  u = halfmod(s, M.half);
-  v = mulmod<KIND>(halfmod(d, M.half), xi, M);
-}
-
-// xi/2 mod q, for gs_bfly_htw.
-__device__ __forceinline__ uint32_t half_tw(uint32_t xi, const Mod32& M) { return halfmod(xi, M.half); }
-
-// gs_bfly_half with the twiddle halved beforehand (xh = xi/2 mod q):
-// (u, v) -> ((u+v)/2, (u-v) xh); in Z_q, (u-v) xh = xi (u-v)/2.
-template <int KIND>
-__device__ __forceinline__ void gs_bfly_htw(uint32_t& u, uint32_t& v, uint32_t xh, const Mod32& M) {
-  const uint32_t s = addmod(u, v, M.q);
-  const uint32_t d = submod(u, v, M.q);
-  u = halfmod(s, M.half);
-  v = mulmod<KIND>(d, xh, M);
 }
 
 }  // namespace pm

@@ -24,14 +24,18 @@
 // words per thread: four times the threads per row, for batches too small
 // to fill the GPU with 16-word threads.
 //
+// Words inside a transform are lazy (lazymod.hpp): each routine states the
+// bounds it takes and leaves, in sixteenths of q. The product's two forward rows
+// run together, round by round, so that they share every twiddle load and
+// companion; the inverse rows scale by 1/N in their last stage.
+//
 // Column pass. One thread per column holds the R = 2^s words of that column
 // in registers and runs the s column stages; twiddles are uniform per launch.
 // In the software-pipelined kernels a 32-word column (s = 5) is held by two
 // lanes of one wave instead, 16 words each (col32_fwd_pair below), so that the
 // column code needs no more registers than the row code beside it.
 #pragma once
-#include "modarith.hpp"
-#include "modarith32.hpp"
+#include "lazymod.hpp"
 
 namespace pm {
 
@@ -107,43 +111,68 @@ __device__ __forceinline__ uint32_t row_base(uint32_t t) {
   return ((t >> P) << (P + EB)) | (t & ((1u << P) - 1u));
 }
 
-// Forward (CT) stages of round RHO on registers x. tw = psi_br of this limb,
-// Rr = R + r for row r of an R-row split.
+// Round 0 of a row held by a whole workgroup: its twiddles are the same for
+// every thread (scalar loads, companions on the scalar unit).
+template <int GEO, int RHO>
+constexpr bool uniform_round() { return RHO == 0 && RowGeom<GEO>::ROWS == 1; }
+
+// Stages of round RHO (TRUNC drops the stride-1 stage).
+template <int GEO, int RHO, bool TRUNC>
+constexpr int round_stages() {
+  return RowGeom<GEO>::hi(RHO) - ((TRUNC && RowGeom<GEO>::lo(RHO) == 0) ? 1 : RowGeom<GEO>::lo(RHO));
+}
+
+// Forward (CT) stages of round RHO on the registers of NX operands x[0..NX)
+// that share every twiddle (and its companion). tw = psi_br of this limb,
+// Rr = R + r for row r of an R-row split; words below B on entry, below
+// ct_bound(B, stages) on return.
 // TRUNC drops the stride-1 stage (the last of Alg. 5): the truncated CT NTT
 // of the fused product (Sec. III-B).
-template <int GEO, int RHO, int KIND, bool TRUNC = false, typename W, typename MT>
-__device__ __forceinline__ void fwd_round(W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
+template <int GEO, int RHO, int KIND, bool TRUNC, int B, int NX, typename W, typename MT>
+__device__ __forceinline__ void fwd_round(W (&x)[NX][RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
                                           uint32_t Rr, const MT& M) {
   using G = RowGeom<GEO>;
-  constexpr int P = G::p(RHO), HI = G::hi(RHO), LO = (TRUNC && G::lo(RHO) == 0) ? 1 : G::lo(RHO), EB = G::EB;
+  constexpr int P = G::p(RHO), HI = G::hi(RHO), LO = HI - round_stages<GEO, RHO, TRUNC>(), EB = G::EB;
+  constexpr bool UNI = uniform_round<GEO, RHO>();
   const uint32_t th = t >> P;
+  int bound = B;
 #pragma unroll
   for (int b = HI - 1; b >= LO; --b) {
     const int jb = b - P;                          // register bit paired at this stage
     const uint32_t mm = 1u << (G::LC - b - 1);      // groups per row at this stage
     const uint32_t base = Rr * mm + (th << (P + EB - b - 1));
+    const CtStage st = ct_stage<W, KIND>(bound, UNI);
 #pragma unroll
     for (int g = 0; g < (G::E >> (jb + 1)); ++g) {
-      const W xi = tw[base + g];
+      const Tw<W> xi = tw_make<KIND, UNI>(tw[base + g], M);
 #pragma unroll
-      for (int s = 0; s < (1 << jb); ++s) {
-        const int j = (g << (jb + 1)) | s;
-        ct_bfly<KIND>(x[j], x[j | (1 << jb)], xi, M);
+      for (int i = 0; i < NX; ++i) {
+#pragma unroll
+        for (int s = 0; s < (1 << jb); ++s) {
+          const int j = (g << (jb + 1)) | s;
+          ct_lazy<KIND>(x[i][j], x[i][j | (1 << jb)], xi, st.red, st.k, M);
+        }
       }
     }
+    bound = st.out;
     stage_fence();
   }
 }
 
-// Inverse (GS, halved) stages of round RHO, smallest stride first. TRUNC drops
-// the stride-1 stage (the first of Alg. 6): the truncated GS NTT of the fused
-// product, whose first stage and its 1/2 are folded into Alg. 7.
-template <int GEO, int RHO, int KIND, bool TRUNC = false, typename W, typename MT>
+// Inverse (GS) stages of round RHO, smallest stride first, on words below BIN
+// (<= LazyRule::GIN); words below GIN on return. The last stage of round 0 (the
+// row's top stride) also scales by 2^-lg, the inverse of the transform's
+// length, so the butterflies need no halving (1/N of Eq. 2 as one factor).
+// TRUNC drops the stride-1 stage (the first of Alg. 6): the truncated GS NTT of
+// the fused product, whose first stage is folded into Alg. 7.
+template <int GEO, int RHO, int KIND, bool TRUNC, int BIN, typename W, typename MT>
 __device__ __forceinline__ void inv_round(W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                          uint32_t Rr, const MT& M) {
+                                          uint32_t Rr, uint32_t lg, const MT& M) {
   using G = RowGeom<GEO>;
-  constexpr int P = G::p(RHO), HI = G::hi(RHO), LO = (TRUNC && G::lo(RHO) == 0) ? 1 : G::lo(RHO), EB = G::EB;
+  constexpr int P = G::p(RHO), HI = G::hi(RHO), LO = HI - round_stages<GEO, RHO, TRUNC>(), EB = G::EB;
+  constexpr bool UNI = uniform_round<GEO, RHO>();
   const uint32_t th = t >> P;
+  GsBounds<W, KIND, G::E> B(BIN);
 #pragma unroll
   for (int b = LO; b < HI; ++b) {
     const int jb = b - P;
@@ -151,11 +180,20 @@ __device__ __forceinline__ void inv_round(W (&x)[RowGeom<GEO>::E], uint32_t t, c
     const uint32_t base = Rr * mm + (th << (P + EB - b - 1));
 #pragma unroll
     for (int g = 0; g < (G::E >> (jb + 1)); ++g) {
-      const W xh = half_tw(tw[base + g], M);     // halved once for its 2^jb butterflies
+      const W xi = tw[base + g];
+      if (RHO == 0 && b == HI - 1) {
+        const W c = inv_pow2<W>(lg, M);
+        const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(xi, c, M), M);
 #pragma unroll
-      for (int s = 0; s < (1 << jb); ++s) {
-        const int j = (g << (jb + 1)) | s;
-        gs_bfly_htw<KIND>(x[j], x[j | (1 << jb)], xh, M);
+        for (int s = 0; s < (1 << jb); ++s)
+          gs_lazy_scaled<KIND>(x[s], x[s | (1 << jb)], tc, tcw, ceil_q(B.b[s | (1 << jb)]), M);
+      } else {
+        const Tw<W> tx = tw_make<KIND, UNI>(xi, M);
+#pragma unroll
+        for (int s = 0; s < (1 << jb); ++s) {
+          const int j = (g << (jb + 1)) | s;
+          gs_track<KIND>(x, B, j, j | (1 << jb), tx, UNI, M);
+        }
       }
     }
     stage_fence();
@@ -218,27 +256,33 @@ __device__ __forceinline__ void exchange(W* lds, W (&x)[RowGeom<GEO>::E], uint32
   lds_get<GEO, TO>(lds, x, t);
 }
 
-// All row stages of the forward transform: rounds 0..NR-1. On return x holds
-// the row in the last round's layout (E consecutive words per thread).
-template <int GEO, int KIND, int RHO = 0, bool TRUNC = false, typename W, typename MT>
-__device__ __forceinline__ void fwd_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                           uint32_t Rr, const MT& M) {
-  fwd_round<GEO, RHO, KIND, TRUNC>(x, t, tw, Rr, M);
+// All row stages of the forward transform of NX rows that share a twiddle row:
+// rounds 0..NR-1. Words below B on entry (at most LazyRule::H); on return x
+// holds the rows in the last round's layout (E consecutive words per thread),
+// below H.
+template <int GEO, int KIND, bool TRUNC, int B, int RHO = 0, int NX, typename W, typename MT>
+__device__ __forceinline__ void fwd_rounds(W* lds, W (&x)[NX][RowGeom<GEO>::E], uint32_t t,
+                                           const W* __restrict__ tw, uint32_t Rr, const MT& M) {
+  fwd_round<GEO, RHO, KIND, TRUNC, B>(x, t, tw, Rr, M);
   if constexpr (RHO + 1 < RowGeom<GEO>::NR) {
-    exchange<GEO, RHO, RHO + 1>(lds, x, t);
-    fwd_rounds<GEO, KIND, RHO + 1, TRUNC>(lds, x, t, tw, Rr, M);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) exchange<GEO, RHO, RHO + 1>(lds, x[i], t);
+    constexpr int BO = ct_bound<W, KIND>(B, round_stages<GEO, RHO, TRUNC>(), uniform_round<GEO, RHO>());
+    fwd_rounds<GEO, KIND, TRUNC, BO, RHO + 1>(lds, x, t, tw, Rr, M);
   }
 }
 
 // All row stages of the inverse transform, from the last round's layout back
-// to round 0's layout.
-template <int GEO, int KIND, int RHO = RowGeom<GEO>::NR - 1, bool TRUNC = false, typename W, typename MT>
+// to round 0's layout, scaled by 2^-lg. Words below BIN on entry, below GIN on
+// return.
+template <int GEO, int KIND, bool TRUNC, int BIN, int RHO = RowGeom<GEO>::NR - 1, typename W, typename MT>
 __device__ __forceinline__ void inv_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                           uint32_t Rr, const MT& M) {
-  inv_round<GEO, RHO, KIND, TRUNC>(x, t, tw, Rr, M);
+                                           uint32_t Rr, uint32_t lg, const MT& M) {
+  static_assert(BIN <= LazyRule<W, KIND>::GIN, "inverse input bound");
+  inv_round<GEO, RHO, KIND, TRUNC, BIN>(x, t, tw, Rr, lg, M);
   if constexpr (RHO > 0) {
     exchange<GEO, RHO, RHO - 1>(lds, x, t);
-    inv_rounds<GEO, KIND, RHO - 1, TRUNC>(lds, x, t, tw, Rr, M);
+    inv_rounds<GEO, KIND, TRUNC, LazyRule<W, KIND>::GIN, RHO - 1>(lds, x, t, tw, Rr, lg, M);
   }
 }
 
@@ -270,84 +314,98 @@ template <int GEO, int KIND, typename W, typename MT>
 __device__ __forceinline__ void fused_hadamard(W (&x)[RowGeom<GEO>::E], const W (&y)[RowGeom<GEO>::E],
                                                const FusedTw<GEO, W>& f, const MT& M) {
   using G = RowGeom<GEO>;
+  using L = LazyRule<W, KIND>;
 #pragma unroll
   for (int j = 0; j < G::E; j += 2) {
-    const W xi = f.v[j >> 2];
-    const W u = mulmod<KIND>(x[j], y[j], M);
-    const W v = mulmod<KIND>(x[j + 1], y[j + 1], M);
-    const W w = mulmod<KIND>(addmod(x[j], x[j + 1], M.q), addmod(y[j], y[j + 1], M.q), M);
-    const W z = mulmod<KIND>(v, xi, M);
-    x[j + 1] = submod(submod(w, u, M.q), v, M.q);
-    x[j] = (j & 2) ? submod(u, z, M.q) : addmod(u, z, M.q);
+    const W a0 = red2<KIND>(x[j], M), a1 = red2<KIND>(x[j + 1], M);
+    const W b0 = red2<KIND>(y[j], M), b1 = red2<KIND>(y[j + 1], M);
+    if constexpr (L::H == 16 * Q1) {
+      // lazy products below PW: c1 = w - u - v + 2 PW < 3 PW, c0 < 2 PW
+      constexpr W kp = ceil_q(L::PW);
+      static_assert(L::PW + 2 * ceil_q(L::PW) * Q1 <= L::H, "headroom of Alg. 7");
+      const W u = mul_lazy2<KIND>(a0, b0, M);
+      const W v = mul_lazy2<KIND>(a1, b1, M);
+      const W w = mul_lazy2<KIND>(red2<KIND>(a0 + a1, M), red2<KIND>(b0 + b1, M), M);
+      const W z = mul_lazy2<KIND>(red2<KIND>(v, M), f.v[j >> 2], M);
+      x[j + 1] = red2<KIND>(w + 2 * kp * M.q - u - v, M);
+      x[j] = red2<KIND>((j & 2) ? u + kp * M.q - z : u + z, M);
+    } else {
+      const W p0 = csub1(a0, M), p1 = csub1(a1, M), r0 = csub1(b0, M), r1 = csub1(b1, M);
+      const W u = mulmod<KIND>(p0, r0, M);
+      const W v = mulmod<KIND>(p1, r1, M);
+      const W w = mulmod<KIND>(addmod(p0, p1, M.q), addmod(r0, r1, M.q), M);
+      const W z = mulmod<KIND>(v, f.v[j >> 2], M);
+      x[j + 1] = submod(submod(w, u, M.q), v, M.q);
+      x[j] = (j & 2) ? submod(u, z, M.q) : addmod(u, z, M.q);
+    }
   }
 }
 
-// Column pass: R = 2^LOGR words of one column (stride C) in registers.
-template <int LOGR, int KIND, typename W, typename MT>
-__device__ __forceinline__ void col_fwd(W (&x)[1 << LOGR], const W* __restrict__ tw, const MT& M) {
+// A radix-2^LOGR block of stages at any depth of Alg. 5 / Alg. 6, its 2^LOGR
+// words in registers. A block of stages s0..s0+LOGR-1 touches 2^LOGR words at
+// stride N >> (s0+LOGR) that share the index bits above bit log2(N) - s0; with
+// h those high bits and rb = 2^s0 + h, stage s0+j's group g (within the block)
+// uses the twiddle at (rb << j) + g. UNI: rb is the same for the whole
+// workgroup. Words below B on entry, below ct_bound(B, LOGR) on return.
+template <int LOGR, int KIND, bool UNI, int B, typename W, typename MT>
+__device__ __forceinline__ void blk_fwd(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, const MT& M) {
   constexpr int R = 1 << LOGR;
+  int bound = B;
 #pragma unroll
   for (int lm = 0; lm < LOGR; ++lm) {
     const int m = 1 << lm, k = R >> (lm + 1);
+    const W* t = tw + (rb << lm);
+    const CtStage st = ct_stage<W, KIND>(bound, UNI);
 #pragma unroll
     for (int g = 0; g < m; ++g) {
-      const W xi = tw[m + g];
+      const Tw<W> xi = tw_make<KIND, UNI>(t[g], M);
 #pragma unroll
-      for (int s = 0; s < k; ++s) ct_bfly<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xi, M);
+      for (int s = 0; s < k; ++s) ct_lazy<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xi, st.red, st.k, M);
+    }
+    bound = st.out;
+  }
+}
+
+// Inverse block on words below BIN (<= GIN); below GIN on return. With
+// scale, its last stage is the transform's last and scales by 2^-lg.
+template <int LOGR, int KIND, bool UNI, int BIN, typename W, typename MT>
+__device__ __forceinline__ void blk_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, bool scale,
+                                        uint32_t lg, const MT& M) {
+  constexpr int R = 1 << LOGR;
+  GsBounds<W, KIND, R> B(BIN);
+#pragma unroll
+  for (int lm = LOGR - 1; lm >= 0; --lm) {
+    const int m = 1 << lm, k = R >> (lm + 1);
+    const W* t = tw + (rb << lm);
+    if (lm == 0 && scale) {
+      const W c = inv_pow2<W>(lg, M);
+      const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(t[0], c, M), M);
+#pragma unroll
+      for (int s = 0; s < k; ++s) gs_lazy_scaled<KIND>(x[s], x[s + k], tc, tcw, ceil_q(B.b[s + k]), M);
+    } else {
+#pragma unroll
+      for (int g = 0; g < m; ++g) {
+        const Tw<W> tx = tw_make<KIND, UNI>(t[g], M);
+#pragma unroll
+        for (int s = 0; s < k; ++s) gs_track<KIND>(x, B, 2 * g * k + s, 2 * g * k + s + k, tx, UNI, M);
+      }
     }
   }
+}
+
+// Column pass: the R = 2^LOGR words of one column (stride C) in registers, the
+// block at depth 0. Forward: canonical words in, below H out (the row pass
+// reduces them). Inverse: the row pass's words (below GIN, already scaled by
+// 1/N) in, canonical words out.
+template <int LOGR, int KIND, typename W, typename MT>
+__device__ __forceinline__ void col_fwd(W (&x)[1 << LOGR], const W* __restrict__ tw, const MT& M) {
+  blk_fwd<LOGR, KIND, true, Q1>(x, tw, 1, M);
 }
 
 template <int LOGR, int KIND, typename W, typename MT>
 __device__ __forceinline__ void col_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, const MT& M) {
-  constexpr int R = 1 << LOGR;
-#pragma unroll
-  for (int lm = LOGR - 1; lm >= 0; --lm) {
-    const int m = 1 << lm, k = R >> (lm + 1);
-#pragma unroll
-    for (int g = 0; g < m; ++g) {
-      const W xh = half_tw(tw[m + g], M);
-#pragma unroll
-      for (int s = 0; s < k; ++s) gs_bfly_htw<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xh, M);
-    }
-  }
-}
-
-// The same radix-2^LOGR block at any depth of Alg. 5 / Alg. 6. A block of
-// stages s0..s0+LOGR-1 touches 2^LOGR words at stride N >> (s0+LOGR) that
-// share the index bits above bit log2(N) - s0; with h those high bits and
-// rb = 2^s0 + h, stage s0+j's group g (within the block) uses the twiddle at
-// (rb << j) + g. col_fwd / col_inv are the case rb = 1.
-template <int LOGR, int KIND, typename W, typename MT>
-__device__ __forceinline__ void blk_fwd(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, const MT& M) {
-  constexpr int R = 1 << LOGR;
-#pragma unroll
-  for (int lm = 0; lm < LOGR; ++lm) {
-    const int m = 1 << lm, k = R >> (lm + 1);
-    const W* t = tw + (rb << lm);
-#pragma unroll
-    for (int g = 0; g < m; ++g) {
-      const W xi = t[g];
-#pragma unroll
-      for (int s = 0; s < k; ++s) ct_bfly<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xi, M);
-    }
-  }
-}
-
-template <int LOGR, int KIND, typename W, typename MT>
-__device__ __forceinline__ void blk_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, const MT& M) {
-  constexpr int R = 1 << LOGR;
-#pragma unroll
-  for (int lm = LOGR - 1; lm >= 0; --lm) {
-    const int m = 1 << lm, k = R >> (lm + 1);
-    const W* t = tw + (rb << lm);
-#pragma unroll
-    for (int g = 0; g < m; ++g) {
-      const W xh = half_tw(t[g], M);
-#pragma unroll
-      for (int s = 0; s < k; ++s) gs_bfly_htw<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xh, M);
-    }
-  }
+  blk_inv<LOGR, KIND, true, LazyRule<W, KIND>::GIN>(x, tw, 1, false, 0, M);
+  canon_all<KIND>(x, M);
 }
 
 // Exchange between the two halves of a wave (v_permlane32_swap, gfx950).
@@ -375,29 +433,32 @@ __device__ __forceinline__ void half_swap(uint64_t& p, uint64_t& q) {
 // are the pairs of that stage. One exchange of eight words (y[8+k] of h = 0
 // with y[k] of h = 1) then leaves half h with rows 16h + j in y[j], the block
 // of rows whose last four column stages use the twiddles of blk_fwd with
-// rb = 2 + h. The inverse (Alg. 6, halved) runs the same steps in reverse
+// rb = 2 + h. The inverse (Alg. 6) runs the same steps in reverse
 // order: the block's four stages, the same exchange, then the stride-16 stage.
 __device__ __forceinline__ uint32_t col32_split_row(int j, uint32_t h) { return (j & 7) + 8 * h + 16 * (j >> 3); }
 __device__ __forceinline__ uint32_t col32_block_row(int j, uint32_t h) { return 16 * h + j; }
 
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void col32_fwd_pair(W (&y)[16], const W* __restrict__ tw, uint32_t h, const MT& M) {
-  const W xi = tw[1];
+  constexpr CtStage st = ct_stage<W, KIND>(Q1, true);
+  const Tw<W> xi = tw_uni<KIND>(tw[1], M);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) ct_bfly<KIND>(y[k], y[8 + k], xi, M);
+  for (int k = 0; k < 8; ++k) ct_lazy<KIND>(y[k], y[8 + k], xi, st.red, st.k, M);
 #pragma unroll
   for (int k = 0; k < 8; ++k) half_swap(y[k], y[8 + k]);
-  blk_fwd<4, KIND>(y, tw, 2 + h, M);
+  blk_fwd<4, KIND, false, st.out>(y, tw, 2 + h, M);
 }
 
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void col32_inv_pair(W (&y)[16], const W* __restrict__ tw, uint32_t h, const MT& M) {
-  blk_inv<4, KIND>(y, tw, 2 + h, M);
+  constexpr int GIN = LazyRule<W, KIND>::GIN;
+  blk_inv<4, KIND, false, GIN>(y, tw, 2 + h, false, 0, M);
 #pragma unroll
   for (int k = 0; k < 8; ++k) half_swap(y[k], y[8 + k]);
-  const W xh = half_tw(tw[1], M);
+  const Tw<W> xi = tw_uni<KIND>(tw[1], M);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) gs_bfly_htw<KIND>(y[k], y[8 + k], xh, M);
+  for (int k = 0; k < 8; ++k) gs_lazy<KIND>(y[k], y[8 + k], xi, ceil_q(GIN), M);
+  canon_all<KIND>(y, M);
 }
 
 }  // namespace pm

@@ -49,7 +49,7 @@ k_pipe(PipeArgsT<W> a, LimbSetT<W> ls) {
     const typename ModOf<W>::type M = ls.mod[limb];
     const W* Bp = (MODE == ROW_SQR) ? nullptr : (a.nops == 1 ? a.C : a.WS) + off;
     row_task<PIPE_LC, KIND, MODE>(a.C + off, Bp, a.C + off, a.twf + (size_t)limb * N, a.twi + (size_t)limb * N,
-                                  R + row, true, M, lds, t);
+                                  R + row, true, false, PIPE_LC + LOGR, M, lds, t);
     return;
   }
   // column workgroups: forward (a -> C, b -> WS) or inverse (C in place)

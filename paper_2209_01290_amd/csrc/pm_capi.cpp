@@ -53,6 +53,13 @@ unsigned log2u(size_t n) { unsigned l = 0; while (((size_t)1 << l) < n) ++l; ret
 
 namespace pm {
 
+// floor(2^(m+64) / q) - 2^64 for m = len(q): 2^(m+64)/q lies in (2^64, 2^65) for
+// a q that is no power of two. By long division, since 2^(m+64) may need 127 bits
+// plus one: 2^(m+64) = (2^m - q) 2^64 + q 2^64, and 2^m - q < q.
+static uint64_t recip_low(uint64_t q, int m) {
+  return (uint64_t)(((u128)(((uint64_t)1 << m) - q) << 64) / q);
+}
+
 // Barrett constants of Alg. 4 for modulus q, in the form the kernels use
 // (see modarith.hpp): mu' = floor(2^(2m+1)/q) << (61-m) for m <= 61.
 bool make_mod(uint64_t q, Mod* M) {
@@ -60,7 +67,7 @@ bool make_mod(uint64_t q, Mod* M) {
   const int m = 64 - __builtin_clzll(q);
   const u128 mu = (((u128)1) << (2 * m + 1)) / q;       // < 2^(m+2)
   M->q = q;
-  M->half = (q >> 1) + 1;                                // (q+1)/2 for odd q
+  M->ml = recip_low(q, m);
   if (m <= 61) {
     M->mu = (uint64_t)(mu << (61 - m));
     M->t = 0;
@@ -91,7 +98,7 @@ bool make_mod32(uint32_t q, Mod32* M) {
   const int m = 32 - __builtin_clz(q);
   const uint64_t mu = ((uint64_t)1 << (2 * m + 1)) / q;
   M->q = q;
-  M->half = (q >> 1) + 1;
+  M->ml = (uint32_t)((((uint64_t)1 << (m + 32)) / q) - ((uint64_t)1 << 32));
   M->s = (uint32_t)(m - 2);
   if (m <= 29) {
     M->mu = (uint32_t)(mu << (29 - m));
@@ -102,6 +109,12 @@ bool make_mod32(uint32_t q, Mod32* M) {
   }
   M->pad = 0;
   return true;
+}
+
+// The butterflies' kind (lazymod.hpp): KIND_WIDE needs 16 q <= 2^64.
+int lazy_kind(const Mod& M) {
+  const int m = 64 - __builtin_clzll(M.q);
+  return (m >= 34 && m <= 60) ? KIND_WIDE : KIND_ANY;
 }
 
 // KIND_WIDE on 32-bit words: every modulus has m <= 29 (no final shift).
@@ -171,20 +184,23 @@ template <> struct Word<uint64_t> {
   static constexpr const char* q_rule = "q must be odd with 3 <= q < 2^62";
   static bool make(uint64_t q, Mod* M) { return (q & 1) && q >= 3 && !(q >> 62) && make_mod(q, M); }
   static int kind(const Mod& M) { return mod_kind(M); }
+  static int lazy(const Mod& M) { return lazy_kind(M); }
 };
 template <> struct Word<uint32_t> {
   static constexpr const char* q_rule = "q must be odd with 3 <= q < 2^30";
   static bool make(uint32_t q, Mod32* M) { return make_mod32(q, M); }
   static int kind(const Mod32& M) { return mod_kind32(M); }
+  static int lazy(const Mod32& M) { return mod_kind32(M); }
 };
 
-// A validated batch: sizes, the per-limb constants, the instantiation kind.
+// A validated batch: sizes, the per-limb constants, the instantiation kinds of
+// the transforms (kind) and of the per-stage path (stage_kind).
 template <typename W>
 struct BatchT {
   size_t N, limbs, polys;
   unsigned log2n;
   std::vector<typename ModOf<W>::type> mods;
-  int kind;
+  int kind, stage_kind;
 };
 
 template <typename W>
@@ -196,14 +212,15 @@ int check_batch(BatchT<W>* b, size_t N, size_t limbs, size_t polys, const W* q) 
   if (!q) return fail(PM_EINVAL, "q (host array of limbs moduli) is null");
   b->N = N; b->limbs = limbs; b->polys = polys; b->log2n = log2u(N);
   b->mods.resize(limbs);
-  b->kind = KIND_WIDE;
+  b->kind = b->stage_kind = KIND_WIDE;
   for (size_t l = 0; l < limbs; ++l) {
     const W ql = q[l];
     if (!Word<W>::make(ql, &b->mods[l]))
       return fail(PM_EINVAL, "limb " + std::to_string(l) + ": " + Word<W>::q_rule);
     if ((ql - 1) % (2 * (uint64_t)N) != 0)
       return fail(PM_EINVAL, "limb " + std::to_string(l) + ": 2N must divide q - 1");
-    if (Word<W>::kind(b->mods[l]) != KIND_WIDE) b->kind = KIND_ANY;
+    if (Word<W>::lazy(b->mods[l]) != KIND_WIDE) b->kind = KIND_ANY;
+    if (Word<W>::kind(b->mods[l]) != KIND_WIDE) b->stage_kind = KIND_ANY;
   }
   return PM_OK;
 }
@@ -306,7 +323,7 @@ int validate_batch(const BatchT<W>& b, std::initializer_list<std::pair<const W*,
   return PM_OK;
 }
 
-// The merged transforms (Alg. 5 / Alg. 6 halved) over a batch, in place.
+// The merged transforms (Alg. 5 / Alg. 6 scaled by 1/N) over a batch, in place.
 template <typename W>
 int ntt_common(W* x, size_t N, size_t limbs, size_t polys, const W* q, const W* tw, pm_stream_t stream, bool inv) {
   BatchT<W> b;
@@ -551,14 +568,14 @@ int pm_polymul_stagewise(const uint64_t* a, const uint64_t* b_, uint64_t* c, siz
     for (unsigned lm = 0; lm < b.log2n; ++lm) {   // Alg. 5, stage m = 2^lm
       ColArgs ca{lm == 0 ? A + base : c + base, c + base, lm == 0 ? B + base : wb, wb, tf, b.log2n,
                  (uint32_t)polys, (uint32_t)nl, square ? 1u : 2u, &ls};
-      if ((e = run_stage(b.kind, false, ca, lm, s)) != hipSuccess) return e;
+      if ((e = run_stage(b.stage_kind, false, ca, lm, s)) != hipSuccess) return e;
     }
-    if ((e = run_pointwise(b.kind, c + base, wb, c + base, b.log2n, (uint32_t)polys, (uint32_t)nl, ls, s)) !=
+    if ((e = run_pointwise(b.stage_kind, c + base, wb, c + base, b.log2n, (uint32_t)polys, (uint32_t)nl, ls, s)) !=
         hipSuccess)
       return e;
     for (int lm = (int)b.log2n - 1; lm >= 0; --lm) {   // Alg. 6, stage m = 2^lm, halved
       ColArgs ca{c + base, c + base, nullptr, nullptr, ti, b.log2n, (uint32_t)polys, (uint32_t)nl, 1, &ls};
-      if ((e = run_stage(b.kind, true, ca, (uint32_t)lm, s)) != hipSuccess) return e;
+      if ((e = run_stage(b.stage_kind, true, ca, (uint32_t)lm, s)) != hipSuccess) return e;
     }
     return hipSuccess;
   });

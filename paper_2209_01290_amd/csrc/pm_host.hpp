@@ -16,6 +16,7 @@ bool make_mod(uint64_t q, Mod* M);
 bool make_mod32(uint32_t q, Mod32* M);
 // Which instantiation a modulus needs (KIND_WIDE or KIND_ANY).
 int mod_kind(const Mod& M);
+int lazy_kind(const Mod& M);     // of the lazily reduced butterflies (lazymod.hpp)
 int mod_kind32(const Mod32& M);
 // Records msg as the calling thread's last error and returns code.
 int set_error(int code, const std::string& msg);

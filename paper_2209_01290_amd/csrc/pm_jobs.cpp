@@ -170,7 +170,7 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
       if (!p || ((uintptr_t)p & 7)) return set_error(PM_EINVAL, tag + "null or misaligned pointer");
     JobDev& J = L->jobs[j];
     make_mod(in.q, &J.mod);
-    if (mod_kind(J.mod) != KIND_WIDE) L->kind = KIND_ANY;
+    if (lazy_kind(J.mod) != KIND_WIDE) L->kind = KIND_ANY;
     J.log2n = in.log2n;
     J.count = in.count;
     // The product is commutative: when c aliases b, swap so that c can only alias a.

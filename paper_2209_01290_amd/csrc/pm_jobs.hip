@@ -82,7 +82,7 @@ __device__ __forceinline__ void job_row(const JobDev& J, uint32_t group, uint64_
   const uint64_t* tf = gmem(J.tf);
   const uint64_t* ti = gmem(J.ti);
   const Mod M = J.mod;
-  row_task<LOGC, KIND, ROW_MUL>(A + off, B + off, Cp + off, tf, ti, R + r, active, M,
+  row_task<LOGC, KIND, ROW_MUL>(A + off, B + off, Cp + off, tf, ti, R + r, active, R == 1, J.log2n, M,
                                 lds_all + (G::NR > 1 ? sub * G::LDS_ROW : 0), t);
 }
 
@@ -136,7 +136,7 @@ __device__ __forceinline__ void pipe_row(const JobDev& J, uint32_t local, uint64
   const uint64_t* tf = gmem(J.tf);
   const uint64_t* ti = gmem(J.ti);
   const Mod M = J.mod;
-  row_task<12, KIND, ROW_MUL>(A + off, B + off, Cp + off, tf, ti, R + row, true, M, lds, t);
+  row_task<12, KIND, ROW_MUL>(A + off, B + off, Cp + off, tf, ti, R + row, true, R == 1, 12 + LOGR, M, lds, t);
 }
 
 // Column work item of the pipelined table: radix R = 2^logr chosen per job;

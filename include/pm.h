@@ -101,12 +101,14 @@ int pm_polymul(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N, size
                const uint64_t *psi_inv_br, void *workspace, pm_stream_t stream);
 
 /*
- * The fused polynomial multiplication of Sec. III-B (Alg. 8): truncated merged
- * CT NTTs of a and b (last stage omitted), the last CT stages, the pointwise
- * product and the first GS stage fused into Alg. 7 on adjacent pairs (four
- * products per pair, twiddle alpha^2 = (-1)^i psi_br[N/4 + i/2]), truncated
- * merged GS NTT (first stage omitted) scaled by 2/N. Same result,
- * arguments and workspace as pm_polymul; N = 2 runs the unfused product.
+ * The fused polynomial multiplication of Sec. III-B (Alg. 8): merged CT NTTs of
+ * a and b without their last stages, the products of the residues that remain as
+ * short polynomials, a merged GS NTT without its first stages. Alg. 8 leaves
+ * out one stage (residues modulo x^2 - alpha^2); on this hardware leaving out
+ * two (residues modulo x^4 - gamma) is faster still, and pm_polymul's rows do the
+ * same wherever the modulus allows it (64-bit words: 34 <= len(q) <= 60, N >= 8). This
+ * entry point keeps 16 words per thread in its rows under every plan. Same
+ * result, arguments and workspace as pm_polymul.
  */
 int pm_polymul_fused(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N, size_t limbs,
                      size_t polys_per_limb, const uint64_t *q, const uint64_t *psi_br,

@@ -48,6 +48,7 @@ struct LazyRule {                            // H = 4
   static constexpr int H = 4 * Q1;
   static constexpr int GIN = 2 * Q1;         // bound on the words between two inverse rounds
   static constexpr int PW = 2 * Q1;          // bound on pointwise products
+  static constexpr int B4 = 2 * Q1;          // bound on the products modulo x^4 - g
   static constexpr int rmax(int, bool) { return 2 * Q1; }
 };
 template <>
@@ -55,6 +56,7 @@ struct LazyRule<uint64_t, KIND_WIDE> {
   static constexpr int H = 16 * Q1;
   static constexpr int GIN = 8 * Q1;
   static constexpr int PW = 72;
+  static constexpr int B4 = 6 * Q1;
   // bound on a twiddle product of a word below v: companion deficit < 2
   // (tw_uni) or < 4 (tw_vec)
   static constexpr int rmax(int v, bool uni) { return 3 * Q1 + ((uni ? 2 : 4) * v + 15) / 16; }
@@ -304,6 +306,92 @@ __device__ __forceinline__ void gs_track(W (&x)[E], GsBounds<W, KIND, E>& B, int
     B.b[i] = 2 * Q1;
   } else {
     B.b[i] = s;
+  }
+}
+
+// ------------------------------------------------- products modulo x^4 - g --
+// a = a b mod (x^4 - g) on polynomials of four coefficients, g = g.w or -g.w
+// (neg). With z = g b (three twiddle products) every coefficient is a sum of four
+// plain products, reduced once.
+
+// 64-bit words, 34 <= len(q) <= 60. The operands are brought below 2q < 2^61 and split
+// into 31 low and 30 high bits, so that the sums of partial products
+// (4 x 2^62, 8 x 2^61, 4 x 2^60) fit 64 bits and need no carries.
+struct Limbs { uint32_t lo, hi; };
+__device__ __forceinline__ Limbs limbs31(uint64_t x) {
+  return {lo32(x) & 0x7fffffffu, __builtin_amdgcn_alignbit(hi32(x), lo32(x), 31)};
+}
+
+// S = c0 + c1 2^31 + c2 2^62 < 16 q^2 to a word below 6q: c = S >> m < 16 q, and
+// with 2^m/q = 1 + ml/2^64 the quotient c + hi64(c ml) falls short of S/q by
+// less than 2 (bits below c) + 1 (ml) + 3 (mulhi_low3).
+__device__ __forceinline__ uint64_t reduce_sum(uint64_t c0, uint64_t c1, uint64_t c2, const Mod& M) {
+  const uint64_t u = c1 + (c0 >> 31);               // < 2^64: c1 < 2^64 - 3 2^33 + 8
+  const uint64_t h = c2 + (u >> 31);                // S >> 62
+  uint64_t s = (uint64_t)lo32(c1) * opaque_s(0x80000000u) + c0;      // S modulo 2^64
+  s = add_high(s, (hi32(c1) << 31) + (lo32(c2) << 30));
+  const uint64_t h2 = h >> 2;                       // S >> 64
+  const uint32_t sh = (uint32_t)len_q(M) - 32;
+  const uint64_t c = pack64(__builtin_amdgcn_alignbit(lo32(h2), hi32(s), sh),
+                            __builtin_amdgcn_alignbit(hi32(h2), lo32(h2), sh));
+  const uint64_t k = c + mulhi_low3(c, M.ml);
+  const uint64_t nq = neg_q(M);
+  return add_high((uint64_t)lo32(k) * lo32(nq) + s, lo32(k) * hi32(nq) + hi32(k) * lo32(nq));
+}
+
+template <int KIND>
+__device__ __forceinline__ void mul_mod_x4(uint64_t (&a)[4], const uint64_t (&b)[4], const Tw<uint64_t>& g, bool neg,
+                                           const Mod& M) {
+  static_assert(KIND == KIND_WIDE, "len(q) <= 60");
+  Limbs A[4], B[4], Z[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t bi = red2<KIND>(b[i], M);
+    A[i] = limbs31(red2<KIND>(a[i], M));
+    B[i] = limbs31(bi);
+    if (i) {
+      const uint64_t z = mul_tw<KIND>(bi, g, (uint64_t)0, M);        // < 3.5 q
+      Z[i] = limbs31(red2<KIND>(neg ? mult_q<uint64_t>(4, M) - z : z, M));
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    uint64_t c0 = 0, c1 = 0, c2 = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const Limbs& v = i <= n ? B[n - i] : Z[4 + n - i];
+      c0 = (uint64_t)A[i].lo * v.lo + c0;
+      c1 = (uint64_t)A[i].lo * v.hi + c1;
+      c1 = (uint64_t)A[i].hi * v.lo + c1;
+      c2 = (uint64_t)A[i].hi * v.hi + c2;
+    }
+    a[n] = reduce_sum(c0, c1, c2, M);
+  }
+}
+
+// 32-bit words: canonical operands, S < 4 q^2 < 2^62; c = S >> m < 4q, the quotient
+// c + hi32(c ml) falls short of S/q by less than 2 + 1 + 1, so r < 4q < 2^32.
+template <int KIND>
+__device__ __forceinline__ void mul_mod_x4(uint32_t (&a)[4], const uint32_t (&b)[4], const Tw<uint32_t>& g, bool neg,
+                                           const Mod32& M) {
+  uint32_t A[4], B[4], Z[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    A[i] = canon<KIND>(a[i], M);
+    B[i] = canon<KIND>(b[i], M);
+    if (i) {
+      const uint32_t z = mul_tw<KIND>(B[i], g, 0u, M);               // < 2q
+      Z[i] = csub1(neg ? 2 * M.q - z : z, M);                         // <= q
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    uint64_t s = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = (uint64_t)A[i] * (i <= n ? B[n - i] : Z[4 + n - i]) + s;
+    const uint32_t c = __builtin_amdgcn_alignbit((uint32_t)(s >> 32), (uint32_t)s, M.s + 2);
+    const uint32_t k = c + __umulhi(c, M.ml);
+    a[n] = red2<KIND>((uint32_t)s - k * M.q, M);
   }
 }
 

@@ -6,13 +6,16 @@
 //   ROW_MUL  the row of a forward, the row of b forward, pointwise product
 //            mod q, inverse; with R = 1 this is all of Eq. 2 for one pair
 //   ROW_SQR  as ROW_MUL with b = a (one forward transform)
-//   ROW_FMUL the fused product of Sec. III-B (Alg. 8): truncated rows of a and
-//            b, Alg. 7 on adjacent pairs, truncated inverse rows
 #pragma once
 #include "ntt_device.hpp"
 #include "pm_internal.hpp"
 
 namespace pm {
+
+template <int GEO, int KIND, typename W>
+constexpr bool product_in_blocks() {
+  return RowGeom<GEO>::LC >= 3 && (sizeof(W) == 4 || KIND == KIND_WIDE);
+}
 
 // Words of a split's row pass (R > 1) come from and go to a column pass in lazy
 // form: below H from the forward columns, below GIN to the inverse columns. With
@@ -23,7 +26,10 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
                                          bool active, bool single, uint32_t lg, const MT& M, W* lds, uint32_t t) {
   using G = RowGeom<GEO>;
   using L = LazyRule<W, KIND>;
-  constexpr int NX = (MODE == ROW_MUL || MODE == ROW_FMUL) ? 2 : 1;
+  constexpr int NX = MODE == ROW_MUL ? 2 : 1;
+  // the product leaves out the two smallest strides of its three transforms
+  // where it can (blk4_mul): not for moduli beyond 60 bits on 64-bit words
+  constexpr int TR = (MODE == ROW_MUL || MODE == ROW_SQR) && product_in_blocks<GEO, KIND, W>() ? 2 : 0;
   W x[NX][G::E];
 #pragma unroll
   for (int i = 0; i < NX; ++i)
@@ -31,28 +37,26 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
     for (int j = 0; j < G::E; ++j) x[i][j] = 0;
   if constexpr (MODE == ROW_INV) {
     if (active) gmem_get<GEO, G::NR - 1>(A, x[0], t);
-    inv_rounds<GEO, KIND, false, Q1>(lds, x[0], t, ti, Rr, lg, M);
+    inv_rounds<GEO, KIND, 0, Q1>(lds, x[0], t, ti, Rr, lg, M);
   } else {
     if (active) gmem_get<GEO, 0>(A, x[0], t);
     if constexpr (NX == 2) {
       if (active) gmem_get<GEO, 0>(B, x[1], t);
     }
-    fwd_rounds<GEO, KIND, MODE == ROW_FMUL, L::H>(lds, x, t, tf, Rr, M);
+    fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tf, Rr, M);
     if constexpr (MODE == ROW_FWD) {
       canon_all<KIND>(x[0], M);
       if (active) gmem_put<GEO, G::NR - 1>(Cout, x[0], t);
       return;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (MODE == ROW_FMUL) {
-      // fused product (Alg. 8): Alg. 7 on adjacent pairs of the truncated rows
-      const FusedTw<GEO, W> ftw = fused_twiddles<GEO>(t, tf, Rr);
-      fused_hadamard<GEO, KIND>(x[0], x[1], ftw, M);
-      inv_rounds<GEO, KIND, true, 2 * Q1>(lds, x[0], t, ti, Rr, lg - 1, M);
+    if constexpr (TR == 2) {
+      blk4_mul<GEO, KIND>(x[0], x[NX - 1], t, tf, Rr, M);         // NX = 1: a = b
+      inv_rounds<GEO, KIND, TR, L::B4>(lds, x[0], t, ti, Rr, lg - TR, M);
     } else {
 #pragma unroll
-      for (int j = 0; j < G::E; ++j) x[0][j] = mul_lazy<KIND>(x[0][j], x[NX - 1][j], M);   // NX = 1: a = b
-      inv_rounds<GEO, KIND, false, L::PW>(lds, x[0], t, ti, Rr, lg, M);
+      for (int j = 0; j < G::E; ++j) x[0][j] = mul_lazy<KIND>(x[0][j], x[NX - 1][j], M);
+      inv_rounds<GEO, KIND, TR, L::PW>(lds, x[0], t, ti, Rr, lg, M);
     }
   }
   if (single) canon_all<KIND>(x[0], M);
@@ -60,9 +64,6 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
 }
 
 // Register budget: 4 waves per SIMD (<= 128 VGPRs).
-template <int MODE>
-struct RowWaves {
-  static constexpr int value = 4;
-};
+constexpr int ROW_WAVES = 4;
 
 }  // namespace pm

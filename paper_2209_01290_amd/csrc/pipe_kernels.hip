@@ -1,4 +1,4 @@
-// Software-pipelined Eq. 2 (and the fused product of Alg. 8) over chunks of
+// Software-pipelined product (Eq. 2) over chunks of
 // the batch's products: the throughput plan with rows of 2^12 words after a
 // column pass of 2^3..2^5 rows (N = 2^15..2^17), 64- or 32-bit words.
 //
@@ -32,10 +32,10 @@ static_assert(pipe_col_blocks(3) == (1u << PIPE_LC) / 256 && pipe_col_blocks(5) 
 // grid: nr row workgroups, then nf forward-column and ni inverse-column ones.
 // A chunk is a range of products (limb-major: product p = limb * polys + poly,
 // stored at p * N), so a chunk may end inside a limb. Every kind of work
-// item fits the row modes' register budget (RowWaves): a column of 8 or 16
+// item fits the row modes' register budget (ROW_WAVES): a column of 8 or 16
 // words is held by one thread, one of 32 words by two lanes.
 template <typename W, int LOGR, int KIND, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RowWaves<MODE>::value, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ROW_WAVES, 8)))
 k_pipe(PipeArgsT<W> a, LimbSetT<W> ls) {
   __shared__ W lds[PG::LDS_WORDS];
   constexpr uint32_t R = 1u << LOGR;
@@ -124,7 +124,6 @@ hipError_t launch_pipe_any(int logr, int mode, const PipeArgsT<W>& a, const Limb
   if (a.nr + a.nf + a.ni == 0) return hipSuccess;
   switch (mode) {
     case ROW_MUL: return pipe_launch_logr<W, ROW_MUL>(logr, a, ls, kind, s);
-    case ROW_FMUL: return pipe_launch_logr<W, ROW_FMUL>(logr, a, ls, kind, s);
     case ROW_SQR: return pipe_launch_logr<W, ROW_SQR>(logr, a, ls, kind, s);
     default: return hipErrorInvalidValue;
   }

@@ -235,7 +235,7 @@ int check_ptr(const void* p, const char* name) {
 }
 
 // Launch wrappers that name each kernel for the event timer:
-// row[32]_<mode>_c<logc>, with a trailing "s" for the small-batch geometry
+// row[32]_<mode>_c<logc> (rows launched by the fused entry points: fmul), with a trailing "s" for the small-batch geometry
 // (4 words per thread), and col[32]_<fwd|inv>_r<logr>.
 template <typename W>
 const char* row_name(int mode, int logc, int ebx) {
@@ -266,9 +266,10 @@ const char* col_name(bool inv, int logr, bool quad) {
   return names[(quad ? 16 : 0) + (inv ? 8 : 0) + logr].c_str();
 }
 
+constexpr int NAME_FMUL = 4;
 template <typename W>
-hipError_t run_row(int logc, int kind, int mode, const RowArgsT<W>& a, hipStream_t s, int ebx = 4) {
-  ProfScope ps(s, row_name<W>(mode, logc, ebx));
+hipError_t run_row(int logc, int kind, int mode, const RowArgsT<W>& a, hipStream_t s, int ebx = 4, bool fused = false) {
+  ProfScope ps(s, row_name<W>(fused ? NAME_FMUL : mode, logc, ebx));
   return launch_row(logc, kind, mode, a, s, ebx);
 }
 
@@ -378,7 +379,9 @@ uint32_t pipe_chunks(size_t np, uint32_t logr) {
   return g > 1 ? (uint32_t)g : 0u;
 }
 
-// Eq. 2 over a batch (fused: Alg. 8's rows instead of the pointwise rows).
+// Eq. 2 over a batch. The rows leave out the two smallest strides of the
+// transforms where the moduli allow it (blk4_mul), so the fused product of
+// Alg. 8, which leaves out one, is the same launch in the 16-word geometry.
 template <typename W>
 int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t polys, const W* q,
                    const W* psi_br, const W* psi_inv_br, void* workspace, pm_stream_t stream, bool fused,
@@ -390,15 +393,12 @@ int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t
       (rc = check_ptr<W>(psi_br, "psi_br")) || (rc = check_ptr<W>(psi_inv_br, "psi_inv_br")))
     return rc;
   const PassPlan p = plan_for(OP_POLYMUL, b.log2n, N * limbs * polys);
-  // the fused product needs N >= 4 (Alg. 8's squared-twiddle identity)
-  fused = fused && b.log2n >= 2;
   const bool same = (a == b_);          // one operand: one column pass, no workspace
-  // and, unfused, one row transform (the small-batch geometry has no squaring
-  // mode: it runs the product with b = a)
-  const bool square = same && !fused && p.ebx == 4;
-  // the fused rows exist in the 16-word geometry only
+  // and one row transform (the small-batch geometry has no squaring mode: it
+  // runs the product with b = a)
   const int ebx = fused ? 4 : (int)p.ebx;
-  const int mode = fused ? ROW_FMUL : (square ? ROW_SQR : ROW_MUL);
+  const bool square = same && ebx == 4;
+  const int mode = square ? ROW_SQR : ROW_MUL;
   // The product is commutative: when c aliases b, swap so that c aliases a.
   const W* A = a;
   const W* B = b_;
@@ -416,7 +416,7 @@ int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t
     if (p.R == 1) {
       RowArgsT<W> ra{A + base, square ? nullptr : B + base, c + base, tf, ti, b.log2n, 1, (uint32_t)polys,
                      (uint32_t)nl, &ls};
-      return run_row(p.logc, b.kind, mode, ra, s, ebx);
+      return run_row(p.logc, b.kind, mode, ra, s, ebx, fused);
     }
     // software-pipelined form: G chunks of products, G + 2 launches (pipe_kernels.hip)
     {
@@ -439,7 +439,7 @@ int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t
           if (j >= 2) pa.i0 = lo(j - 2), pa.ni = cbs * (lo(j - 1) - lo(j - 2));
           static const char* const names[2][3] = {{"pipe32_mul_c12", "pipe32_fmul_c12", "pipe32_sqr_c12"},
                                                   {"pipe_mul_c12", "pipe_fmul_c12", "pipe_sqr_c12"}};
-          ProfScope ps(s, names[sizeof(W) == 8][mode == ROW_FMUL ? 1 : (mode == ROW_SQR ? 2 : 0)]);
+          ProfScope ps(s, names[sizeof(W) == 8][fused ? 1 : (square ? 2 : 0)]);
           hipError_t e = launch_pipe((int)p.logr, mode, pa, ls, b.kind, s);
           if (e != hipSuccess) return e;
         }
@@ -454,7 +454,7 @@ int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t
     if (e != hipSuccess) return e;
     RowArgsT<W> ra{c + base, square ? nullptr : wb, c + base, tf, ti, b.log2n, p.R, (uint32_t)polys,
                    (uint32_t)nl, &ls};
-    if ((e = run_row(p.logc, b.kind, mode, ra, s, ebx)) != hipSuccess) return e;
+    if ((e = run_row(p.logc, b.kind, mode, ra, s, ebx, fused)) != hipSuccess) return e;
     ColArgsT<W> ci{c + base, c + base, nullptr, nullptr, ti, b.log2n, (uint32_t)polys, (uint32_t)nl, 1, &ls};
     return run_col(p.logr, b.kind, true, ci, s, p.ebx);
   });

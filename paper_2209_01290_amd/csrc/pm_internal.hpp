@@ -27,7 +27,7 @@ static_assert(sizeof(LimbSetT<uint64_t>) <= 2048 && sizeof(LimbSetT<uint32_t>) <
 using LimbSet = LimbSetT<uint64_t>;
 using LimbSet32 = LimbSetT<uint32_t>;
 
-enum { ROW_FWD = 0, ROW_INV = 1, ROW_MUL = 2, ROW_SQR = 3, ROW_FMUL = 4 };
+enum { ROW_FWD = 0, ROW_INV = 1, ROW_MUL = 2, ROW_SQR = 3 };
 
 // Column workgroups (256 threads) per operand of one product in the
 // software-pipelined kernels (rows of 2^12 words, column radix 2^logr): one
@@ -72,7 +72,7 @@ hipError_t launch_row(int logc, int kind, int mode, const RowArgsT<uint32_t>& a,
 PM_DECL_ROW(1) PM_DECL_ROW(2) PM_DECL_ROW(3) PM_DECL_ROW(4) PM_DECL_ROW(5) PM_DECL_ROW(6) PM_DECL_ROW(7)
 PM_DECL_ROW(8) PM_DECL_ROW(9) PM_DECL_ROW(10) PM_DECL_ROW(11) PM_DECL_ROW(12) PM_DECL_ROW(13) PM_DECL_ROW(14)
 #undef PM_DECL_ROW
-// The product rows (ROW_MUL, ROW_FMUL) of 2^12 words with the split's radix
+// The product rows (ROW_MUL) of 2^12 words with the split's radix
 // fixed at compile time (row_fixed.inc): 64-bit words with moduli of 34..61
 // bits (row_12r.hip), 32-bit words (row_12r32.hip); false, launching
 // nothing, for other modes, kinds or shapes.

@@ -1,4 +1,4 @@
-// Software-pipelined Eq. 2 and fused product (pipe_kernels.hip): one launch
+// Software-pipelined product (pipe_kernels.hip): one launch
 // runs the row pass of one chunk of products, the forward column pass of the
 // next chunk and the inverse column pass of the chunk before.
 #pragma once
@@ -28,8 +28,7 @@ struct PipeArgsT {
   uint32_t nops;
 };
 
-// logr in 3..5; mode: ROW_MUL (Eq. 2), ROW_FMUL (Alg. 8's rows) or ROW_SQR
-// (Eq. 2 with a = b, one forward row transform).
+// logr in 3..5; mode: ROW_MUL or ROW_SQR (a = b, one forward row transform).
 hipError_t launch_pipe(int logr, int mode, const PipeArgsT<uint64_t>& a, const LimbSetT<uint64_t>& ls, int kind,
                        hipStream_t s);
 hipError_t launch_pipe(int logr, int mode, const PipeArgsT<uint32_t>& a, const LimbSetT<uint32_t>& ls, int kind,

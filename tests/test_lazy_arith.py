@@ -61,6 +61,52 @@ def test_bounds_64(m):
             assert 0 <= 2 * (a * b - _mulhi_low3(cc, mu) * q) < 9 * q
 
 
+def _x4(a, b, g, q):
+    """Coefficients of a b mod (x^4 - g), as whole numbers (sums of four products each)."""
+    z = [g * v % q for v in b]
+    return [sum(a[i] * (b[n - i] if i <= n else z[4 + n - i]) for i in range(4)) for n in range(4)]
+
+
+@pytest.mark.parametrize("m", [34, 35, 47, 59, 60])
+def test_block_product_64(m):
+    """Sums of four products of words below 2q: the limb sums fit 64 bits and the
+    reduction leaves a word below 6q."""
+    rnd = random.Random(m)
+    M31 = (1 << 31) - 1
+    for q in {(1 << m) - 1, (1 << (m - 1)) + 1, rnd.randrange(1 << (m - 1), 1 << m) | 1}:
+        ml = ((1 << (m + 64)) // q) - (1 << 64)
+        for _ in range(100):
+            a = [_edge(rnd, 2 * q) for _ in range(4)]
+            b = [_edge(rnd, 2 * q) for _ in range(4)]
+            c0 = sum((x & M31) * (y & M31) for x, y in zip(a, b))
+            c1 = sum((x & M31) * (y >> 31) + (x >> 31) * (y & M31) for x, y in zip(a, b))
+            c2 = sum((x >> 31) * (y >> 31) for x, y in zip(a, b))
+            assert max(c0, c1, c2) < 1 << 64
+            u = c1 + (c0 >> 31)
+            h = c2 + (u >> 31)
+            S = sum(x * y for x, y in zip(a, b))
+            assert u < 1 << 64 and h == S >> 62 and h < 1 << 64
+            c = S >> m
+            assert c < 1 << 64
+            k = c + _mulhi_low3(c, ml)
+            assert k < 1 << 64 and 0 <= S - k * q < 6 * q
+
+
+@pytest.mark.parametrize("m", [3, 17, 29, 30])
+def test_block_product_32(m):
+    rnd = random.Random(m)
+    for q in {(1 << m) - 1, (1 << (m - 1)) + 1, rnd.randrange(1 << (m - 1), 1 << m) | 1}:
+        ml = ((1 << (m + 32)) // q) - (1 << 32)
+        for _ in range(100):
+            a = [_edge(rnd, q) for _ in range(4)]
+            b = [_edge(rnd, q) for _ in range(4)]
+            for S in _x4(a, b, _edge(rnd, q), q):
+                c = S >> m
+                assert S < 1 << 64 and c < 1 << 32
+                k = c + _hi(c * ml)
+                assert k < 1 << 32 and 0 <= S - k * q < 4 * q < 1 << 32
+
+
 @pytest.mark.parametrize("bits,m", [(64, 2), (64, 33), (64, 61), (64, 62), (32, 3), (32, 29), (32, 30)])
 def test_bounds_four_q(bits, m):
     """Harvey's rule: exact companions (32-bit words up to 29 bits: short by

@@ -35,6 +35,8 @@
 // lanes of one wave instead, 16 words each (col32_fwd_pair below), so that the
 // column code needs no more registers than the row code beside it.
 #pragma once
+#include <type_traits>
+
 #include "lazymod.hpp"
 
 namespace pm {
@@ -134,20 +136,46 @@ __device__ __forceinline__ uint32_t round_block(uint32_t t, uint32_t Rr, int p) 
   return (Rr << (G::LC - G::EB - p)) + (t >> p);
 }
 
+// Where a round's twiddles come from: TwMem reads each when its stage comes up;
+// TwRegs holds all of the round's, loaded ahead (before the exchange that
+// precedes the round, whose barriers then hide the latency). The transforms' rows
+// use TwRegs (15 words beside the 16 of the row), the product's, which hold two
+// rows, TwMem: with TwRegs they spill.
+template <int EB, typename W>
+struct TwMem {
+  const W* __restrict__ tw;
+  uint32_t rb;
+  __device__ __forceinline__ TwMem(const W* __restrict__ t, uint32_t r, int, int) : tw(t), rb(r) {}
+  __device__ __forceinline__ W operator()(int jb, int g) const { return tw[(rb << (EB - 1 - jb)) + g]; }
+};
+template <int EB, typename W>
+struct TwRegs {
+  W v[1 << EB];
+  __device__ __forceinline__ TwRegs() {}
+  __device__ __forceinline__ TwRegs(const W* __restrict__ tw, uint32_t rb, int jlo, int jhi) {
+#pragma unroll
+    for (int jb = 0; jb < EB; ++jb)
+      if (jb >= jlo && jb < jhi) {
+#pragma unroll
+        for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) v[(1 << (EB - 1 - jb)) + g] = tw[(rb << (EB - 1 - jb)) + g];
+      }
+  }
+  __device__ __forceinline__ W operator()(int jb, int g) const { return v[(1 << (EB - 1 - jb)) + g]; }
+};
+
 // Forward (CT) stages pairing register bits [JLO, JHI), largest first, on the
 // registers of NX operands x[0..NX) that share every twiddle (and its
 // companion). tw = psi_br of this limb; words below B on entry, below
 // ct_bound(B, JHI - JLO) on return.
-template <int EB, int JLO, int JHI, int KIND, bool UNI, int B, int NX, typename W, typename MT>
-__device__ __forceinline__ void fwd_block(W (&x)[NX][1 << EB], uint32_t rb, const W* __restrict__ tw, const MT& M) {
+template <int EB, int JLO, int JHI, int KIND, bool UNI, int B, int NX, typename W, typename TW, typename MT>
+__device__ __forceinline__ void fwd_block(W (&x)[NX][1 << EB], const TW& tw, const MT& M) {
   int bound = B;
 #pragma unroll
   for (int jb = JHI - 1; jb >= JLO; --jb) {
-    const uint32_t base = rb << (EB - 1 - jb);
     const CtStage st = ct_stage<W, KIND>(bound, UNI);
 #pragma unroll
     for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) {
-      const Tw<W> xi = tw_make<KIND, UNI>(tw[base + g], M);
+      const Tw<W> xi = tw_make<KIND, UNI>(tw(jb, g), M);
 #pragma unroll
       for (int i = 0; i < NX; ++i) {
 #pragma unroll
@@ -158,7 +186,7 @@ __device__ __forceinline__ void fwd_block(W (&x)[NX][1 << EB], uint32_t rb, cons
       }
     }
     bound = st.out;
-    stage_fence();
+    if (EB == 4) stage_fence();
   }
 }
 
@@ -167,16 +195,14 @@ __device__ __forceinline__ void fwd_block(W (&x)[NX][1 << EB], uint32_t rb, cons
 // ends with the row's top stride, whose stage also scales by 2^-lg, the inverse
 // of the transform's length (1/N of Eq. 2 as one factor, no halving in the
 // butterflies).
-template <int EB, int JLO, int JHI, int KIND, bool UNI, int BIN, bool LAST, typename W, typename MT>
-__device__ __forceinline__ void inv_block(W (&x)[1 << EB], uint32_t rb, const W* __restrict__ tw, uint32_t lg,
-                                          const MT& M) {
+template <int EB, int JLO, int JHI, int KIND, bool UNI, int BIN, bool LAST, typename W, typename TW, typename MT>
+__device__ __forceinline__ void inv_block(W (&x)[1 << EB], const TW& tw, uint32_t lg, const MT& M) {
   GsBounds<W, KIND, 1 << EB> B(BIN);
 #pragma unroll
   for (int jb = JLO; jb < JHI; ++jb) {
-    const uint32_t base = rb << (EB - 1 - jb);
 #pragma unroll
     for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) {
-      const W xi = tw[base + g];
+      const W xi = tw(jb, g);
       if (LAST && jb == JHI - 1) {
         const W c = inv_pow2<W>(lg, M);
         const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(xi, c, M), M);
@@ -192,32 +218,59 @@ __device__ __forceinline__ void inv_block(W (&x)[1 << EB], uint32_t rb, const W*
         }
       }
     }
-    stage_fence();
+    if (EB == 4) stage_fence();
   }
 }
 
-// Round RHO of the forward row transform without the stages of the TR smallest
-// strides (the last of Alg. 5): the truncated CT NTT of a product whose residues
-// are multiplied as short polynomials (blk4_mul).
-template <int GEO, int RHO, int KIND, int TR, int B, int NX, typename W, typename MT>
-__device__ __forceinline__ void fwd_round(W (&x)[NX][RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                          uint32_t Rr, const MT& M) {
+// Register bits [JLO, JHI) of round RHO's stages when the TR smallest strides
+// are left out.
+template <int GEO, int RHO, int TR>
+struct Round {
   using G = RowGeom<GEO>;
-  constexpr int P = G::p(RHO), JHI = G::hi(RHO) - P;
-  fwd_block<G::EB, JHI - round_stages<GEO, RHO, TR>(), JHI, KIND, uniform_round<GEO, RHO>(), B>(
-      x, round_block<GEO>(t, Rr, P), tw, M);
-}
+  static constexpr int P = G::p(RHO), JHI = G::hi(RHO) - P, JLO = JHI - round_stages<GEO, RHO, TR>();
+  static constexpr bool UNI = uniform_round<GEO, RHO>();
+  template <typename TW, typename W>
+  static __device__ __forceinline__ TW twiddles(uint32_t t, const W* __restrict__ tw, uint32_t Rr) {
+    return TW(tw, round_block<GEO>(t, Rr, P), JLO, JHI);
+  }
+};
 
-// Round RHO of the inverse row transform without the stages of the TR smallest
-// strides (the first of Alg. 6).
-template <int GEO, int RHO, int KIND, int TR, int BIN, typename W, typename MT>
-__device__ __forceinline__ void inv_round(W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                          uint32_t Rr, uint32_t lg, const MT& M) {
+// Twiddle sources of a row transform's rounds, get<RHO>() called before the exchange that
+// precedes round RHO.
+// RowTwAll (4 words per thread, calls bound by latency): every round's twiddles
+// (three per thread and round) loaded when the kernel starts, beside its data.
+template <int GEO, int TR, typename W>
+struct RowTwAll {
   using G = RowGeom<GEO>;
-  constexpr int P = G::p(RHO), JHI = G::hi(RHO) - P;
-  inv_block<G::EB, JHI - round_stages<GEO, RHO, TR>(), JHI, KIND, uniform_round<GEO, RHO>(), BIN, RHO == 0>(
-      x, round_block<GEO>(t, Rr, P), tw, lg, M);
-}
+  using TW = TwRegs<G::EB, W>;
+  TW r[G::NR];
+  template <int RHO>
+  __device__ __forceinline__ void load(uint32_t t, const W* __restrict__ tw, uint32_t Rr) {
+    r[RHO] = Round<GEO, RHO, TR>::template twiddles<TW>(t, tw, Rr);
+    if constexpr (RHO + 1 < G::NR) load<RHO + 1>(t, tw, Rr);
+  }
+  __device__ __forceinline__ RowTwAll(uint32_t t, const W* __restrict__ tw, uint32_t Rr) { load<0>(t, tw, Rr); }
+  template <int RHO>
+  __device__ __forceinline__ const TW& get() const { return r[RHO]; }
+};
+// RowTwRound (16 words per thread): a round's at a time; NX = 1: ahead of the
+// round (TwRegs), NX = 2: each as its stage comes up (TwMem).
+template <int GEO, int TR, int NX, typename W>
+struct RowTwRound {
+  using G = RowGeom<GEO>;
+  uint32_t t, Rr;
+  const W* __restrict__ tw;
+  __device__ __forceinline__ RowTwRound(uint32_t t_, const W* __restrict__ tw_, uint32_t Rr_)
+      : t(t_), Rr(Rr_), tw(tw_) {}
+  template <int RHO>
+  __device__ __forceinline__ auto get() const {
+    using TW = typename std::conditional<NX == 1 && !uniform_round<GEO, RHO>(), TwRegs<G::EB, W>, TwMem<G::EB, W>>::type;
+    return Round<GEO, RHO, TR>::template twiddles<TW>(t, tw, Rr);
+  }
+};
+template <int GEO, int TR, int NX, typename W>
+using RowTw = typename std::conditional<RowGeom<GEO>::EBX == 2 && (RowGeom<GEO>::NR > 1), RowTwAll<GEO, TR, W>,
+                                        RowTwRound<GEO, TR, NX, W>>::type;
 
 // LDS exchanges only run for rows of at least two rounds, where every round's
 // register bits are EB = EBX wide; a single-round row (c <= EBX) has P = 0
@@ -275,35 +328,39 @@ __device__ __forceinline__ void exchange(W* lds, W (&x)[RowGeom<GEO>::E], uint32
   lds_get<GEO, TO>(lds, x, t);
 }
 
-// All row stages of the forward transform of NX rows that share a twiddle row:
-// rounds 0..NR-1. Words below B on entry (at most LazyRule::H); on return x
-// holds the rows in the last round's layout (E consecutive words per thread),
-// below H.
-template <int GEO, int KIND, int TR, int B, int RHO = 0, int NX, typename W, typename MT>
-__device__ __forceinline__ void fwd_rounds(W* lds, W (&x)[NX][RowGeom<GEO>::E], uint32_t t,
-                                           const W* __restrict__ tw, uint32_t Rr, const MT& M) {
+// All row stages of the forward transform of NX rows that share a twiddle row,
+// without the stages of the TR smallest strides (the last of Alg. 5): rounds
+// RHO..NR-1. Words below B on entry (at most LazyRule::H); on return x holds the
+// rows in the last round's layout (E consecutive words per thread), below H.
+template <int GEO, int KIND, int TR, int B, int RHO = 0, int NX, typename W, typename TW, typename MT>
+__device__ __forceinline__ void fwd_rounds(W* lds, W (&x)[NX][RowGeom<GEO>::E], uint32_t t, const TW& tws,
+                                           const MT& M) {
   using G = RowGeom<GEO>;
-  fwd_round<GEO, RHO, KIND, TR, B>(x, t, tw, Rr, M);
-  if constexpr (RHO + 1 < G::NR) {
+  using R = Round<GEO, RHO, TR>;
+  const auto tr = tws.template get<RHO>();
+  if constexpr (RHO > 0) {
 #pragma unroll
-    for (int i = 0; i < NX; ++i) exchange<GEO, RHO, RHO + 1>(lds, x[i], t);
-    constexpr int BO = ct_bound<W, KIND>(B, round_stages<GEO, RHO, TR>(), uniform_round<GEO, RHO>());
-    fwd_rounds<GEO, KIND, TR, BO, RHO + 1>(lds, x, t, tw, Rr, M);
+    for (int i = 0; i < NX; ++i) exchange<GEO, RHO - 1, RHO>(lds, x[i], t);
   }
+  fwd_block<G::EB, R::JLO, R::JHI, KIND, R::UNI, B>(x, tr, M);
+  if constexpr (RHO + 1 < G::NR)
+    fwd_rounds<GEO, KIND, TR, ct_bound<W, KIND>(B, R::JHI - R::JLO, R::UNI), RHO + 1>(lds, x, t, tws, M);
 }
 
-// All row stages of the inverse transform, from the last round's layout back
-// to round 0's layout, scaled by 2^-lg. Words below BIN on entry, below GIN on
-// return.
-template <int GEO, int KIND, int TR, int BIN, int RHO = RowGeom<GEO>::NR - 1, typename W, typename MT>
-__device__ __forceinline__ void inv_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint32_t t, const W* __restrict__ tw,
-                                           uint32_t Rr, uint32_t lg, const MT& M) {
+// All row stages of the inverse transform without those of the TR smallest
+// strides (the first of Alg. 6), from the last round's layout back to round
+// 0's layout, scaled by 2^-lg: rounds RHO..0. Words below BIN on entry, below GIN
+// on return.
+template <int GEO, int KIND, int TR, int BIN, int RHO = RowGeom<GEO>::NR - 1, typename W, typename TW, typename MT>
+__device__ __forceinline__ void inv_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint32_t t, const TW& tws, uint32_t lg,
+                                           const MT& M) {
   static_assert(BIN <= LazyRule<W, KIND>::GIN, "inverse input bound");
-  inv_round<GEO, RHO, KIND, TR, BIN>(x, t, tw, Rr, lg, M);
-  if constexpr (RHO > 0) {
-    exchange<GEO, RHO, RHO - 1>(lds, x, t);
-    inv_rounds<GEO, KIND, TR, LazyRule<W, KIND>::GIN, RHO - 1>(lds, x, t, tw, Rr, lg, M);
-  }
+  using G = RowGeom<GEO>;
+  using R = Round<GEO, RHO, TR>;
+  const auto tr = tws.template get<RHO>();
+  if constexpr (RHO + 1 < G::NR) exchange<GEO, RHO + 1, RHO>(lds, x, t);
+  inv_block<G::EB, R::JLO, R::JHI, KIND, R::UNI, BIN, RHO == 0>(x, tr, lg, M);
+  if constexpr (RHO > 0) inv_rounds<GEO, KIND, TR, LazyRule<W, KIND>::GIN, RHO - 1>(lds, x, t, tws, lg, M);
 }
 
 // Product of the truncated rows (TR = 2): with the strides 2 and 1 left out, four
@@ -318,15 +375,24 @@ __device__ __forceinline__ void inv_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint
 // rows of 2^12 words 6,310 -> 5,560 VALU instructions a thread.
 // x = x y for the E consecutive words of a thread (last round's layout), rows of
 // at least 8 words; products below LazyRule::B4.
-template <int GEO, int KIND, typename W, typename MT>
-__device__ __forceinline__ void blk4_mul(W (&x)[RowGeom<GEO>::E], const W (&y)[RowGeom<GEO>::E], uint32_t t,
-                                         const W* __restrict__ tw, uint32_t Rr, const MT& M) {
+template <int GEO, typename W>
+struct Blk4Tw {
   using G = RowGeom<GEO>;
   static_assert(G::LC >= 3 && G::E >= 4, "blocks of four words in rows of at least eight");
-  const uint32_t base = Rr * (1u << (G::LC - 3)) + ((t << G::EB) >> 3);
+  W v[(G::E + 7) / 8];
+  __device__ __forceinline__ Blk4Tw(uint32_t t, const W* __restrict__ tw, uint32_t Rr) {
+    const uint32_t base = Rr * (1u << (G::LC - 3)) + ((t << G::EB) >> 3);
+#pragma unroll
+    for (int i = 0; i < (G::E + 7) / 8; ++i) v[i] = tw[base + i];
+  }
+};
+template <int GEO, int KIND, typename W, typename MT>
+__device__ __forceinline__ void blk4_mul(W (&x)[RowGeom<GEO>::E], const W (&y)[RowGeom<GEO>::E],
+                                         const Blk4Tw<GEO, W>& gs, uint32_t t, const MT& M) {
+  using G = RowGeom<GEO>;
 #pragma unroll
   for (int j = 0; j < G::E; j += 4) {
-    const Tw<W> g = tw_vec<KIND>(tw[base + (j >> 3)], M);
+    const Tw<W> g = tw_vec<KIND>(gs.v[j >> 3], M);
     const bool neg = G::E >= 8 ? (j & 4) != 0 : (t & 1) != 0;
     W a[4] = {x[j], x[j + 1], x[j + 2], x[j + 3]}, b[4] = {y[j], y[j + 1], y[j + 2], y[j + 3]};
     mul_mod_x4<KIND>(a, b, g, neg, M);

@@ -10,8 +10,9 @@
 // grid row (blockIdx.y), so its twiddles are uniform across the workgroup.
 //
 // Words between the passes of one transform are lazy (below LazyRule's H on the
-// way forward, below GIN on the way back); the last pass makes them canonical,
-// and the inverse's last stage scales by 1/N.
+// way forward, below GIN on the way back); the last pass of a transform or a product
+// makes them canonical (LAST). The 1/N scaling is in the last stage of an
+// inverse transform (SCALE) or of the product's fused block.
 //
 //   IL_FWD  stages of Alg. 5 on one or two operands (A -> C, B -> D)
 //   IL_INV  stages of Alg. 6 (A -> C)
@@ -25,10 +26,15 @@
 
 namespace pm {
 
-template <int LOGR> struct IlWaves { static constexpr int value = LOGR >= 5 ? 2 : 4; };
+// Waves per SIMD: a block of 2^6 words needs 128 VGPRs for its data (3 waves), the
+// fused block of 2^5 words per operand as many (2 waves).
+template <int LOGR, int MODE>
+struct IlWaves {
+  static constexpr int value = MODE == IL_MUL ? (LOGR == 5 ? 2 : 4) : (LOGR >= 5 ? 3 : 5);
+};
 
-template <int LOGR, int KIND, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(IlWaves<LOGR>::value + (MODE != IL_MUL), 8)))
+template <int LOGR, int KIND, int MODE, bool LAST, bool SCALE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((IlWaves<LOGR, MODE>::value), 8)))
 k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint64_t* __restrict__ twf,
      const uint64_t* __restrict__ twi, uint32_t log2n, uint32_t s0, uint32_t polys, uint32_t nops, LimbSet ls) {
   constexpr int R = 1 << LOGR;
@@ -55,7 +61,7 @@ k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint6
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (src + i * step)[lane];
     blk_fwd<LOGR, KIND, true, H>(x, twf + (size_t)limb * N, rb, M);
-    if (s0 + LOGR == log2n) canon_all<KIND>(x, M);      // the transform's last block
+    if (LAST) canon_all<KIND>(x, M);
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   } else if constexpr (MODE == IL_INV) {
@@ -63,45 +69,54 @@ k_il(const uint64_t* A, const uint64_t* B, uint64_t* C, uint64_t* D, const uint6
     uint64_t* dst = C + base;
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (src + i * step)[lane];
-    blk_inv<LOGR, KIND, true, L::GIN>(x, twi + (size_t)limb * N, rb, s0 == 0, log2n, M);
-    if (s0 == 0) canon_all<KIND>(x, M);
+    blk_inv<LOGR, KIND, true, L::GIN, SCALE>(x, twi + (size_t)limb * N, rb, log2n, M);
+    if (LAST) canon_all<KIND>(x, M);
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   } else {
+    constexpr int TR = LOGR >= 3 && KIND == KIND_WIDE ? 2 : 0;      // as product_in_blocks
     const uint64_t* tf = twf + (size_t)limb * N;
     const uint64_t* sa = A + base;
     const uint64_t* sb = B + base;
     uint64_t* dst = C + base;
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = (sa + i * step)[lane];
-    blk_fwd<LOGR, KIND, true, H>(x, tf, rb, M);
+    blk_fwd<LOGR, KIND, true, H, TR>(x, tf, rb, M);
     uint64_t y[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) y[i] = (sb + i * step)[lane];
-    blk_fwd<LOGR, KIND, true, H>(y, tf, rb, M);
-#pragma unroll
-    for (int i = 0; i < R; ++i) x[i] = mul_lazy<KIND>(x[i], y[i], M);
-    blk_inv<LOGR, KIND, true, L::PW>(x, twi + (size_t)limb * N, rb, s0 == 0, log2n, M);
-    if (s0 == 0) canon_all<KIND>(x, M);
+    blk_fwd<LOGR, KIND, true, H, TR>(y, tf, rb, M);
+    blk_mul<LOGR, KIND, true, TR>(x, y, tf, rb, M);
+    blk_inv<LOGR, KIND, true, TR == 2 ? L::B4 : L::PW, SCALE, TR>(x, twi + (size_t)limb * N, rb, log2n - TR, M);
+    if (LAST) canon_all<KIND>(x, M);
 #pragma unroll
     for (int i = 0; i < R; ++i) (dst + i * step)[lane] = x[i];
   }
 }
 
-template <int LOGR, int KIND, int MODE>
+template <int LOGR, int KIND, int MODE, bool LAST, bool SCALE>
 static void il_launch(const IlArgs& a, hipStream_t s) {
   const uint32_t bs = a.polys >= 256 ? 256u : ((a.polys + 63) / 64) * 64;
   const uint32_t nz = (MODE == IL_FWD) ? a.limbs * a.nops : a.limbs;
   dim3 grid((a.polys + bs - 1) / bs, 1u << (a.log2n - LOGR), nz);
-  hipLaunchKernelGGL((k_il<LOGR, KIND, MODE>), grid, dim3(bs), 0, s, a.A, a.B, a.C, a.D, a.twf, a.twi, a.log2n,
-                     a.s0, a.polys, a.nops, *a.ls);
+  hipLaunchKernelGGL((k_il<LOGR, KIND, MODE, LAST, SCALE>), grid, dim3(bs), 0, s, a.A, a.B, a.C, a.D, a.twf, a.twi,
+                     a.log2n, a.s0, a.polys, a.nops, *a.ls);
 }
 
 template <int LOGR, int KIND>
 static void il_launch_mode(const IlArgs& a, int mode, hipStream_t s) {
-  if (mode == IL_FWD) il_launch<LOGR, KIND, IL_FWD>(a, s);
-  else if (mode == IL_INV) il_launch<LOGR, KIND, IL_INV>(a, s);
-  else if constexpr (LOGR <= IL_MUL_MAXR) il_launch<LOGR, KIND, IL_MUL>(a, s);
+  const bool first = a.s0 == 0, last = a.s0 + LOGR == a.log2n;   // block of the first / last stages of Alg. 5
+  if (mode == IL_FWD) {
+    if (last) il_launch<LOGR, KIND, IL_FWD, true, false>(a, s);
+    else il_launch<LOGR, KIND, IL_FWD, false, false>(a, s);
+  } else if (mode == IL_INV) {
+    if (!first) il_launch<LOGR, KIND, IL_INV, false, false>(a, s);
+    else if (a.scale) il_launch<LOGR, KIND, IL_INV, true, true>(a, s);
+    else il_launch<LOGR, KIND, IL_INV, true, false>(a, s);
+  } else if constexpr (LOGR <= IL_MUL_MAXR) {
+    if (first) il_launch<LOGR, KIND, IL_MUL, true, true>(a, s);
+    else il_launch<LOGR, KIND, IL_MUL, false, true>(a, s);
+  }
 }
 
 template <int LOGR>

@@ -46,6 +46,9 @@ namespace pm {
 // more threads per row), clear = rounds of four stages with 16 words per
 // thread. For the 16-word geometry GEO = c.
 constexpr int row_geo(int logc, int ebx) { return logc | (ebx == 2 ? 32 : 0); }
+// bit 6: workgroups of at least 256 threads, several rows each (the job
+// tables' row kernel, one workgroup size for every row length)
+constexpr int ROW_GEO_SHARED = 64;
 
 template <int GEO>
 struct RowGeom {
@@ -56,11 +59,17 @@ struct RowGeom {
   static constexpr int LOGT = LC - EB;
   static constexpr int T = 1 << LOGT;                  // threads per row
   static constexpr int NR = LC <= EBX ? 1 : (LC + EBX - 1) / EBX;   // rounds
-  static constexpr int WGMIN = EBX == 4 ? 256 : 64;
+  // rows shorter than a workgroup share one only below a wave: a row with its own
+  // workgroup waits for no other row and has scalar twiddles in round 0
+  static constexpr int WGMIN = (GEO & ROW_GEO_SHARED) ? 256 : 64;
   static constexpr int WG = T < WGMIN ? WGMIN : T;     // threads per workgroup
   static constexpr int ROWS = WG / T;                  // rows per workgroup
   static constexpr int LDS_ROW = (1 << LC) + ((1 << LC) >> 4);  // padded words
-  static constexpr int LDS_WORDS = NR > 1 ? ROWS * LDS_ROW : 1;
+  // rows of 2^12 words keep round 1's 240 twiddles and companions beside the row
+  // (TwLds): 38.9 KB, still four workgroups to a CU's 160 KB
+  static constexpr bool TW_LDS = LC == 12 && EBX == 4;
+  static constexpr int LDS_TW = TW_LDS ? 2 * T : 0;
+  static constexpr int LDS_WORDS = NR > 1 ? ROWS * LDS_ROW + LDS_TW : 1;
   // register-bit base p and butterfly bits [lo, hi) of round rho (forward order)
   static constexpr int hi(int rho) { return LC - EBX * rho; }
   static constexpr int lo(int rho) { return hi(rho) - EBX > 0 ? hi(rho) - EBX : 0; }
@@ -136,17 +145,24 @@ __device__ __forceinline__ uint32_t round_block(uint32_t t, uint32_t Rr, int p) 
   return (Rr << (G::LC - G::EB - p)) + (t >> p);
 }
 
-// Where a round's twiddles come from: TwMem reads each when its stage comes up;
+// Where a round's twiddles and companions come from: TwMem reads each when its stage comes up;
 // TwRegs holds all of the round's, loaded ahead (before the exchange that
 // precedes the round, whose barriers then hide the latency). The transforms' rows
 // use TwRegs (15 words beside the 16 of the row), the product's, which hold two
-// rows, TwMem: with TwRegs they spill.
+// rows, TwMem: with TwRegs they spill. TwLds: round 1 of a 2^12-word row, where 16
+// threads share each twiddle: every thread makes one companion (load_tw_lds)
+// and reads fifteen from LDS instead of making fifteen (product rows 174 -> 168
+// in VALU cost, -3 %).
 template <int EB, typename W>
 struct TwMem {
   const W* __restrict__ tw;
   uint32_t rb;
   __device__ __forceinline__ TwMem(const W* __restrict__ t, uint32_t r, int, int) : tw(t), rb(r) {}
-  __device__ __forceinline__ W operator()(int jb, int g) const { return tw[(rb << (EB - 1 - jb)) + g]; }
+  __device__ __forceinline__ W raw(int jb, int g) const { return tw[(rb << (EB - 1 - jb)) + g]; }
+  template <int KIND, bool UNI, typename MT>
+  __device__ __forceinline__ Tw<W> get(int jb, int g, const MT& M) const {
+    return tw_make<KIND, UNI>(raw(jb, g), M);
+  }
 };
 template <int EB, typename W>
 struct TwRegs {
@@ -160,8 +176,34 @@ struct TwRegs {
         for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) v[(1 << (EB - 1 - jb)) + g] = tw[(rb << (EB - 1 - jb)) + g];
       }
   }
-  __device__ __forceinline__ W operator()(int jb, int g) const { return v[(1 << (EB - 1 - jb)) + g]; }
+  __device__ __forceinline__ W raw(int jb, int g) const { return v[(1 << (EB - 1 - jb)) + g]; }
+  template <int KIND, bool UNI, typename MT>
+  __device__ __forceinline__ Tw<W> get(int jb, int g, const MT& M) const {
+    return tw_make<KIND, UNI>(raw(jb, g), M);
+  }
 };
+// Round 1 of a 2^12-word row (register base 4): stage s of the round has the
+// twiddles (Rr << (4+s)) + [0, 16 << s), kept at slot (16 << s) + i - 16; a thread's
+// group g of it is slot ((16 + t/16) << s) + g - 16.
+template <typename W>
+struct TwLds {
+  const Tw<W>* p;      // slots of the thread's row of the table
+  uint32_t r16;        // 16 + t/16
+  __device__ __forceinline__ W raw(int, int) const { return 0; }      // (never the row's last stage)
+  template <int KIND, bool UNI, typename MT>
+  __device__ __forceinline__ Tw<W> get(int jb, int g, const MT&) const { return p[(r16 << (3 - jb)) + g - 16]; }
+};
+// The word of slot t (slots from 240 on are not read), and its entry with the
+// companion; every thread writes one, so that no branch is needed.
+template <typename W>
+__device__ __forceinline__ W tw_lds_word(const W* __restrict__ tw, uint32_t t, uint32_t Rr) {
+  const uint32_t j = t < 240 ? t + 16 : 16, s = 27 - __builtin_clz(j);      // floor(log2 j) - 4
+  return tw[(Rr << (4 + s)) + j - (16u << s)];
+}
+template <int KIND, typename W, typename MT>
+__device__ __forceinline__ void tw_lds_put(Tw<W>* table, W w, uint32_t t, const MT& M) {
+  table[t] = tw_vec<KIND>(w, M);
+}
 
 // Forward (CT) stages pairing register bits [JLO, JHI), largest first, on the
 // registers of NX operands x[0..NX) that share every twiddle (and its
@@ -175,7 +217,7 @@ __device__ __forceinline__ void fwd_block(W (&x)[NX][1 << EB], const TW& tw, con
     const CtStage st = ct_stage<W, KIND>(bound, UNI);
 #pragma unroll
     for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) {
-      const Tw<W> xi = tw_make<KIND, UNI>(tw(jb, g), M);
+      const Tw<W> xi = tw.template get<KIND, UNI>(jb, g, M);
 #pragma unroll
       for (int i = 0; i < NX; ++i) {
 #pragma unroll
@@ -202,15 +244,15 @@ __device__ __forceinline__ void inv_block(W (&x)[1 << EB], const TW& tw, uint32_
   for (int jb = JLO; jb < JHI; ++jb) {
 #pragma unroll
     for (int g = 0; g < (1 << (EB - 1 - jb)); ++g) {
-      const W xi = tw(jb, g);
       if (LAST && jb == JHI - 1) {
+        const W xi = tw.raw(jb, g);
         const W c = inv_pow2<W>(lg, M);
         const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(xi, c, M), M);
 #pragma unroll
         for (int s = 0; s < (1 << jb); ++s)
           gs_lazy_scaled<KIND>(x[s], x[s | (1 << jb)], tc, tcw, ceil_q(B.b[s | (1 << jb)]), M);
       } else {
-        const Tw<W> tx = tw_make<KIND, UNI>(xi, M);
+        const Tw<W> tx = tw.template get<KIND, UNI>(jb, g, M);
 #pragma unroll
         for (int s = 0; s < (1 << jb); ++s) {
           const int j = (g << (jb + 1)) | s;
@@ -249,7 +291,9 @@ struct RowTwAll {
     r[RHO] = Round<GEO, RHO, TR>::template twiddles<TW>(t, tw, Rr);
     if constexpr (RHO + 1 < G::NR) load<RHO + 1>(t, tw, Rr);
   }
-  __device__ __forceinline__ RowTwAll(uint32_t t, const W* __restrict__ tw, uint32_t Rr) { load<0>(t, tw, Rr); }
+  __device__ __forceinline__ RowTwAll(uint32_t t, const W* __restrict__ tw, uint32_t Rr, const Tw<W>*) {
+    load<0>(t, tw, Rr);
+  }
   template <int RHO>
   __device__ __forceinline__ const TW& get() const { return r[RHO]; }
 };
@@ -260,10 +304,16 @@ struct RowTwRound {
   using G = RowGeom<GEO>;
   uint32_t t, Rr;
   const W* __restrict__ tw;
-  __device__ __forceinline__ RowTwRound(uint32_t t_, const W* __restrict__ tw_, uint32_t Rr_)
-      : t(t_), Rr(Rr_), tw(tw_) {}
+  const Tw<W>* table;         // round 1's twiddles in LDS (RowGeom::TW_LDS)
+  __device__ __forceinline__ RowTwRound(uint32_t t_, const W* __restrict__ tw_, uint32_t Rr_, const Tw<W>* table_)
+      : t(t_), Rr(Rr_), tw(tw_), table(table_) {}
   template <int RHO>
   __device__ __forceinline__ auto get() const {
+    if constexpr (G::TW_LDS && RHO == 1) return TwLds<W>{table, 16 + (t >> 4)};
+    else return get_mem<RHO>();
+  }
+  template <int RHO>
+  __device__ __forceinline__ auto get_mem() const {
     using TW = typename std::conditional<NX == 1 && !uniform_round<GEO, RHO>(), TwRegs<G::EB, W>, TwMem<G::EB, W>>::type;
     return Round<GEO, RHO, TR>::template twiddles<TW>(t, tw, Rr);
   }
@@ -406,50 +456,71 @@ __device__ __forceinline__ void blk4_mul(W (&x)[RowGeom<GEO>::E], const W (&y)[R
 // stride N >> (s0+LOGR) that share the index bits above bit log2(N) - s0; with
 // h those high bits and rb = 2^s0 + h, stage s0+j's group g (within the block)
 // uses the twiddle at (rb << j) + g. UNI: rb is the same for the whole
-// workgroup. Words below B on entry, below ct_bound(B, LOGR) on return.
-template <int LOGR, int KIND, bool UNI, int B, typename W, typename MT>
+// workgroup. Words below B on entry, below ct_bound(B, LOGR) on return. TR: without
+// the block's TR smallest strides.
+template <int LOGR, int KIND, bool UNI, int B, int TR = 0, int LM = 0, typename W, typename MT>
 __device__ __forceinline__ void blk_fwd(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, const MT& M) {
-  constexpr int R = 1 << LOGR;
-  int bound = B;
+  constexpr int m = 1 << LM, k = (1 << LOGR) >> (LM + 1);
+  constexpr CtStage st = ct_stage<W, KIND>(B, UNI);
+  const W* t = tw + (rb << LM);
 #pragma unroll
-  for (int lm = 0; lm < LOGR; ++lm) {
-    const int m = 1 << lm, k = R >> (lm + 1);
-    const W* t = tw + (rb << lm);
-    const CtStage st = ct_stage<W, KIND>(bound, UNI);
+  for (int g = 0; g < m; ++g) {
+    const Tw<W> xi = tw_make<KIND, UNI>(t[g], M);
 #pragma unroll
-    for (int g = 0; g < m; ++g) {
-      const Tw<W> xi = tw_make<KIND, UNI>(t[g], M);
-#pragma unroll
-      for (int s = 0; s < k; ++s) ct_lazy<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xi, st.red, st.k, M);
-    }
-    bound = st.out;
+    for (int s = 0; s < k; ++s) ct_lazy<KIND>(x[2 * g * k + s], x[2 * g * k + s + k], xi, st.red, st.k, M);
+    if (LOGR >= 5) stage_fence();      // registers: no butterflies of the next group ahead
   }
+  if constexpr (LM + 1 < LOGR - TR) blk_fwd<LOGR, KIND, UNI, st.out, TR, LM + 1>(x, tw, rb, M);
 }
 
-// Inverse block on words below BIN (<= GIN); below GIN on return. With
-// scale, its last stage is the transform's last and scales by 2^-lg.
-template <int LOGR, int KIND, bool UNI, int BIN, typename W, typename MT>
-__device__ __forceinline__ void blk_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, bool scale,
-                                        uint32_t lg, const MT& M) {
-  constexpr int R = 1 << LOGR;
-  GsBounds<W, KIND, R> B(BIN);
+// Inverse block on words with the bounds B (at most GIN on entry and on return).
+// SCALE: its last stage is the transform's last and scales by 2^-lg.
+template <int LOGR, int KIND, bool UNI, bool SCALE, int LM, typename W, typename MT>
+__device__ __forceinline__ void blk_inv_stage(W (&x)[1 << LOGR], GsBounds<W, KIND, 1 << LOGR>& B,
+                                              const W* __restrict__ tw, uint32_t rb, uint32_t lg, const MT& M) {
+  constexpr int m = 1 << LM, k = (1 << LOGR) >> (LM + 1);
+  const W* t = tw + (rb << LM);
+  if constexpr (LM == 0 && SCALE) {
+    const W c = inv_pow2<W>(lg, M);
+    const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(t[0], c, M), M);
 #pragma unroll
-  for (int lm = LOGR - 1; lm >= 0; --lm) {
-    const int m = 1 << lm, k = R >> (lm + 1);
-    const W* t = tw + (rb << lm);
-    if (lm == 0 && scale) {
-      const W c = inv_pow2<W>(lg, M);
-      const Tw<W> tc = tw_uni<KIND>(c, M), tcw = tw_make<KIND, UNI>(mulmod<KIND>(t[0], c, M), M);
+    for (int s = 0; s < k; ++s) gs_lazy_scaled<KIND>(x[s], x[s + k], tc, tcw, ceil_q(B.b[s + k]), M);
+  } else {
 #pragma unroll
-      for (int s = 0; s < k; ++s) gs_lazy_scaled<KIND>(x[s], x[s + k], tc, tcw, ceil_q(B.b[s + k]), M);
-    } else {
+    for (int g = 0; g < m; ++g) {
+      const Tw<W> tx = tw_make<KIND, UNI>(t[g], M);
 #pragma unroll
-      for (int g = 0; g < m; ++g) {
-        const Tw<W> tx = tw_make<KIND, UNI>(t[g], M);
-#pragma unroll
-        for (int s = 0; s < k; ++s) gs_track<KIND>(x, B, 2 * g * k + s, 2 * g * k + s + k, tx, UNI, M);
-      }
+      for (int s = 0; s < k; ++s) gs_track<KIND>(x, B, 2 * g * k + s, 2 * g * k + s + k, tx, UNI, M);
+      if (LOGR >= 5) stage_fence();
     }
+  }
+  if constexpr (LM > 0) blk_inv_stage<LOGR, KIND, UNI, SCALE, LM - 1>(x, B, tw, rb, lg, M);
+}
+template <int LOGR, int KIND, bool UNI, int BIN, bool SCALE, int TR = 0, typename W, typename MT>
+__device__ __forceinline__ void blk_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, uint32_t rb, uint32_t lg,
+                                        const MT& M) {
+  GsBounds<W, KIND, 1 << LOGR> B(BIN);
+  blk_inv_stage<LOGR, KIND, UNI, SCALE, LOGR - 1 - TR>(x, B, tw, rb, lg, M);
+}
+
+// x = x y for a block that ends with stride 1 (forward stages but TR done), words
+// J and up: modulo x^4 - g as blk4_mul (TR = 2), or pointwise. Recursive: the
+// largest block's loop is beyond what the compiler unrolls.
+template <int LOGR, int KIND, bool UNI, int TR, int J = 0, typename W, typename MT>
+__device__ __forceinline__ void blk_mul(W (&x)[1 << LOGR], const W (&y)[1 << LOGR], const W* __restrict__ tw,
+                                        uint32_t rb, const MT& M) {
+  if constexpr (TR == 2) {
+    static_assert(LOGR >= 3, "a stage of stride 4 in the block");
+    const Tw<W> g = tw_make<KIND, UNI>(tw[(rb << (LOGR - 3)) + (J >> 3)], M);
+    W a[4] = {x[J], x[J + 1], x[J + 2], x[J + 3]}, b[4] = {y[J], y[J + 1], y[J + 2], y[J + 3]};
+    mul_mod_x4<KIND>(a, b, g, (J & 4) != 0, M);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[J + i] = a[i];
+    stage_fence();
+    if constexpr (J + 4 < (1 << LOGR)) blk_mul<LOGR, KIND, UNI, TR, J + 4>(x, y, tw, rb, M);
+  } else {
+    x[J] = mul_lazy<KIND>(x[J], y[J], M);
+    if constexpr (J + 1 < (1 << LOGR)) blk_mul<LOGR, KIND, UNI, TR, J + 1>(x, y, tw, rb, M);
   }
 }
 
@@ -464,7 +535,7 @@ __device__ __forceinline__ void col_fwd(W (&x)[1 << LOGR], const W* __restrict__
 
 template <int LOGR, int KIND, typename W, typename MT>
 __device__ __forceinline__ void col_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, const MT& M) {
-  blk_inv<LOGR, KIND, true, LazyRule<W, KIND>::GIN>(x, tw, 1, false, 0, M);
+  blk_inv<LOGR, KIND, true, LazyRule<W, KIND>::GIN, false>(x, tw, 1, 0, M);
   canon_all<KIND>(x, M);
 }
 
@@ -512,7 +583,7 @@ __device__ __forceinline__ void col32_fwd_pair(W (&y)[16], const W* __restrict__
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void col32_inv_pair(W (&y)[16], const W* __restrict__ tw, uint32_t h, const MT& M) {
   constexpr int GIN = LazyRule<W, KIND>::GIN;
-  blk_inv<4, KIND, false, GIN>(y, tw, 2 + h, false, 0, M);
+  blk_inv<4, KIND, false, GIN, false>(y, tw, 2 + h, 0, M);
 #pragma unroll
   for (int k = 0; k < 8; ++k) half_swap(y[k], y[8 + k]);
   const Tw<W> xi = tw_uni<KIND>(tw[1], M);

@@ -1,5 +1,5 @@
 // One row task of the row pass (see ntt_device.hpp), shared by the batch
-// kernels (row_kernel.inc) and the job-table kernels (pm_jobs.hip).
+// kernels (row_kernel.inc) and the job-table kernels (jobs_kernels.inc).
 //
 //   ROW_FWD  the last c stages of Alg. 5 on one row, in place
 //   ROW_INV  the first c stages of Alg. 6 (scaled by 1/N), in place
@@ -38,26 +38,33 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
   // the product leaves out the two smallest strides of its three transforms
   // where it can (blk4_mul): not for moduli beyond 60 bits on 64-bit words
   constexpr int TR = (MODE == ROW_MUL || MODE == ROW_SQR) && product_in_blocks<GEO, KIND, W>() ? 2 : 0;
+  Tw<W>* const table = (Tw<W>*)(lds + (G::TW_LDS ? G::LDS_ROW : 0));
   W x[NX][G::E];
 #pragma unroll
   for (int i = 0; i < NX; ++i)
 #pragma unroll
     for (int j = 0; j < G::E; ++j) x[i][j] = 0;
   if constexpr (MODE == ROW_INV) {
-    const RowTw<GEO, 0, 1, W> tws(t, ti, Rr);
+    W tl = 0;
+    if constexpr (G::TW_LDS) tl = tw_lds_word(ti, t, Rr);
+    const RowTw<GEO, 0, 1, W> tws(t, ti, Rr, table);
     if constexpr (exchange_io<GEO>()) {
       if (active) gmem_get<GEO, 0>(A, x[0], t);
       exchange<GEO, 0, G::NR - 1>(lds, x[0], t);
     } else {
       if (active) gmem_get<GEO, G::NR - 1>(A, x[0], t);
     }
+    if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, tl, t, M);
     inv_rounds<GEO, KIND, 0, Q1>(lds, x[0], t, tws, lg, M);
   } else {
+    W tl = 0;
+    if constexpr (G::TW_LDS) tl = tw_lds_word(tf, t, Rr);
     if (active) gmem_get<GEO, 0>(A, x[0], t);
     if constexpr (NX == 2) {
       if (active) gmem_get<GEO, 0>(B, x[1], t);
     }
-    const RowTw<GEO, TR, NX, W> tws(t, tf, Rr);
+    const RowTw<GEO, TR, NX, W> tws(t, tf, Rr, table);
+    if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, tl, t, M);      // read after round 0's exchange
     if constexpr (MODE == ROW_FWD) {
       fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
       canon_all<KIND>(x[0], M);
@@ -69,18 +76,25 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
       }
       return;
     } else {
-      const RowTw<GEO, TR, 1, W> iws(t, ti, Rr);
+      const RowTw<GEO, TR, 1, W> iws(t, ti, Rr, table);
       if constexpr (TR == 2) {
         const Blk4Tw<GEO, W> gs(t, tf, Rr);
         fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
         __builtin_amdgcn_sched_barrier(0);
+        W il = 0;
+        if constexpr (G::TW_LDS) il = tw_lds_word(ti, t, Rr);
         blk4_mul<GEO, KIND>(x[0], x[NX - 1], gs, t, M);         // NX = 1: a = b
+        // the forward table's last reads are behind round 2's exchange
+        if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, il, t, M);
         inv_rounds<GEO, KIND, TR, L::B4>(lds, x[0], t, iws, lg - TR, M);
       } else {
         fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
         __builtin_amdgcn_sched_barrier(0);
+        W il = 0;
+        if constexpr (G::TW_LDS) il = tw_lds_word(ti, t, Rr);
 #pragma unroll
         for (int j = 0; j < G::E; ++j) x[0][j] = mul_lazy<KIND>(x[0][j], x[NX - 1][j], M);
+        if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, il, t, M);
         inv_rounds<GEO, KIND, TR, L::PW>(lds, x[0], t, iws, lg, M);
       }
     }

@@ -37,7 +37,7 @@ static_assert(pipe_col_blocks(3) == (1u << PIPE_LC) / 256 && pipe_col_blocks(5) 
 template <typename W, int LOGR, int KIND, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ROW_WAVES, 8)))
 k_pipe(PipeArgsT<W> a, LimbSetT<W> ls) {
-  __shared__ W lds[PG::LDS_WORDS];
+  __shared__ alignas(16) W lds[PG::LDS_WORDS];
   constexpr uint32_t R = 1u << LOGR;
   constexpr uint32_t CB = pipe_col_blocks(LOGR);
   const size_t N = (size_t)1 << (PIPE_LC + LOGR), C = (size_t)1 << PIPE_LC;

@@ -65,14 +65,21 @@ static uint64_t recip_low(uint64_t q, int m) {
 bool make_mod(uint64_t q, Mod* M) {
   if (q < 2 || (q >> 62) != 0) return false;
   const int m = 64 - __builtin_clzll(q);
-  const u128 mu = (((u128)1) << (2 * m + 1)) / q;       // < 2^(m+2)
   M->q = q;
-  M->ml = recip_low(q, m);
+  uint64_t mu;                                           // floor(2^(2m+1)/q) < 2^(m+2)
+  if (q & (q - 1)) {
+    M->ml = recip_low(q, m);
+    // 2^(2m+1)/q = (2^(m+64)/q) / 2^(63-m), floors of floors
+    mu = (M->ml >> (63 - m)) | ((uint64_t)1 << (m + 1));
+  } else {
+    M->ml = 0;                                           // (elementwise products only)
+    mu = (uint64_t)1 << (m + 2);                         // q = 2^(m-1)
+  }
   if (m <= 61) {
-    M->mu = (uint64_t)(mu << (61 - m));
+    M->mu = mu << (61 - m);
     M->t = 0;
   } else {
-    M->mu = (uint64_t)mu;
+    M->mu = mu;
     M->t = 1;
   }
   if (m >= 34) { M->wide = 1; M->s1 = (uint32_t)(m - 34); }
@@ -619,7 +626,8 @@ int pm_polymul_fused_u32(const uint32_t* a, const uint32_t* b, uint32_t* c, size
 // each one launch over the whole batch; n stages split into the fewest
 // blocks of at most IL_MAXR stages, balanced, larger blocks first; the fused
 // middle block of the product holds two operands and takes at most
-// IL_MUL_MAXR stages.
+// IL_MUL_MAXR stages (6 stages in it fit one wave per SIMD only: N = 2^12 x 999 as
+// 6 + 6 instead of 4 + 4 + 4 stages took 108 us against 103).
 
 static int il_plan(unsigned n, int maxlast, int* sizes) {
   int np = (int)((n + IL_MAXR - 1) / IL_MAXR);
@@ -661,7 +669,7 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   rc = for_chunks(b, [&](size_t l0, size_t nl, const LimbSet& ls) -> hipError_t {
     uint64_t* xs = x + l0 * polys * N;
     const uint64_t* t = tw + l0 * N;
-    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls};
+    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls, true};
     hipError_t e;
     if (!inv) {
       for (int k = 0; k < np; ++k) {

@@ -95,6 +95,7 @@ struct IlArgs {
   const uint64_t* twi;           // psi_inv_br, [limbs][N]
   uint32_t log2n, s0, polys, limbs, nops;
   const LimbSet* ls;
+  bool scale = false;            // IL_INV of a transform: the block of stage 0 scales by 1/N
 };
 hipError_t launch_il(int logr, int kind, int mode, const IlArgs& a, hipStream_t s);
 
@@ -105,12 +106,6 @@ hipError_t launch_canon(const void* x, int word_bytes, size_t per_limb, uint32_t
 hipError_t launch_stage(int kind, bool inv, const ColArgs& a, uint32_t log2m, hipStream_t s);
 hipError_t launch_pointwise(int kind, const uint64_t* A, const uint64_t* B, uint64_t* C, uint32_t log2n,
                             uint32_t polys, uint32_t limbs, const LimbSet& ls, hipStream_t s);
-
-// Job-table passes (pm_jobs.hip): phase PH_COLF / PH_ROW / PH_COLI, the row
-// phase split by maximal row length (12, 13 or 14).
-struct JobDev;
-hipError_t launch_jobs(int phase, int maxlogc, int kind, const JobDev* jobs, const uint32_t* item_job,
-                       uint32_t nitems, hipStream_t s);
 
 // Barrett variant study (barrett_study.hip, barrett_study_host.cpp).
 struct RedParams {

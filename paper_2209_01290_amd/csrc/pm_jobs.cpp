@@ -270,6 +270,18 @@ void fill_blob(const Layout& L, char* host, char* dev_base) {
     if (!L.map[g].empty()) std::memcpy(host + L.off_map[g], L.map[g].data(), L.map[g].size() * sizeof(uint32_t));
 }
 
+hipError_t launch_jobs(int phase, int maxlogc, int kind, const JobDev* jobs, const uint32_t* item_job, uint32_t nitems,
+                       hipStream_t s) {
+  return kind == KIND_WIDE ? launch_jobs_wide(phase, maxlogc, jobs, item_job, nitems, s)
+                           : launch_jobs_any(phase, maxlogc, jobs, item_job, nitems, s);
+}
+
+hipError_t launch_jobs_pipe(int kind, const JobDev* jobs, const uint32_t* map_row, const uint32_t* map_colf,
+                            const uint32_t* map_coli, const JobsPipeLaunch& L, hipStream_t s) {
+  return kind == KIND_WIDE ? launch_jobs_pipe_wide(jobs, map_row, map_colf, map_coli, L, s)
+                           : launch_jobs_pipe_any(jobs, map_row, map_colf, map_coli, L, s);
+}
+
 hipError_t launch_all(const Layout& L, char* dev_base, hipStream_t s, bool timed) {
   const JobDev* jobs = (const JobDev*)dev_base;
   auto map = [&](int g) { return (const uint32_t*)(dev_base + L.off_map[g]); };

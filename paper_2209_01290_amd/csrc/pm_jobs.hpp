@@ -30,7 +30,14 @@ struct JobsPipeLaunch {
   uint32_t r0, nr, f0, nf, i0, ni;
 };
 
-hipError_t launch_jobs_pipe(int kind, const JobDev* jobs, const uint32_t* map_row, const uint32_t* map_colf,
-                            const uint32_t* map_coli, const JobsPipeLaunch& L, hipStream_t s);
+// One kind's launchers (jobs_wide.hip, jobs_any.hip); row passes (phase PH_ROW) by
+// maximal row length 2^maxlogc, 11..14.
+#define PM_DECL_JOBS(K)                                                                                        \
+  hipError_t launch_jobs_##K(int phase, int maxlogc, const JobDev* jobs, const uint32_t* item_job,             \
+                             uint32_t nitems, hipStream_t s);                                                  \
+  hipError_t launch_jobs_pipe_##K(const JobDev* jobs, const uint32_t* map_row, const uint32_t* map_colf,       \
+                                  const uint32_t* map_coli, const JobsPipeLaunch& L, hipStream_t s);
+PM_DECL_JOBS(wide) PM_DECL_JOBS(any)
+#undef PM_DECL_JOBS
 
 }  // namespace pm

@@ -186,6 +186,18 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
   const int set = g_jobs_pipe.load();
   const bool pipelined = set != 0 && set != 1 && pipe_rows >= (set > 1 ? 1 : JOBS_PIPE_MIN_ROWS);
   const std::vector<uint32_t> order = table_order(L->jobs);
+  // Three-pass form: rows of up to 2^11 words and of 2^12 words are two launches. A
+  // batch that would need both takes rows of 2^12 words for every N >= 2^12
+  // instead: a short batch's launches each leave most of the GPU idle (five
+  // requests of N = 2^13..2^17: 23 + 59 us of rows as two launches), and a long one
+  // loses little to its tuned short rows.
+  bool rows11 = false, rows12 = false;
+  for (const JobDev& J : L->jobs) {
+    if (J.log2n < 12) continue;
+    const uint32_t logc = plan_for(OP_POLYMUL, J.log2n).logc;
+    rows11 |= logc <= 11;
+    rows12 |= logc == 12;
+  }
   size_t ws = 0;
   std::vector<size_t> ws_job(njobs, 0);
   std::vector<uint32_t> pjobs;
@@ -198,8 +210,8 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
       pjobs.push_back((uint32_t)j);
     } else {
       const PassPlan p = plan_for(OP_POLYMUL, J.log2n);
-      J.logc = p.logc;
-      J.logr = p.logr;
+      J.logc = (rows11 && rows12 && J.log2n >= 12 && p.logc <= 11) ? 12 : p.logc;
+      J.logr = J.log2n - J.logc;
     }
     if (J.logr > 0 && J.nops == 2) {
       ws_job[j] = ws;

@@ -11,6 +11,7 @@ Streams: ``stream=None`` uses torch's current stream on the tensor's device.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 import threading
@@ -25,6 +26,21 @@ OP_NTT_FWD, OP_NTT_INV, OP_POLYMUL = 0, 1, 2
 
 _lock = threading.Lock()
 _lib = None
+_torch_module = None
+_raw_stream = None          # torch's current raw stream of a device index, where it offers one
+_DTYPES = {}
+
+
+def _torch():
+    """torch, imported on first use (the module itself needs no device)."""
+    global _torch_module, _raw_stream
+    if _torch_module is None:
+        import torch
+        _DTYPES[64] = frozenset((torch.int64, torch.uint64))
+        _DTYPES[32] = frozenset((torch.int32, torch.uint32))
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch_module = torch
+    return _torch_module
 
 
 class ProbeEntry(ctypes.Structure):
@@ -144,13 +160,20 @@ def _check(rc: int, func: str):
         raise PMError(rc, func, load().pm_last_error().decode())
 
 
+def _is(t, dtypes):
+    """A contiguous device tensor of one of these types (one look for the usual case)."""
+    return t.is_cuda and t.dtype in dtypes and t.is_contiguous()
+
+
 def _dptr(t, name):
     """Device pointer of a contiguous 64-bit tensor (None -> NULL)."""
     if t is None:
         return None
-    import torch
+    torch = _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch tensor" % name)
+    if _is(t, _DTYPES[64]):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError("%s must live on a HIP device" % name)
     if t.element_size() != 8 or t.dtype.is_floating_point:
@@ -164,9 +187,11 @@ def _dptr32(t, name):
     """Device pointer of a contiguous 32-bit integer tensor (None -> NULL)."""
     if t is None:
         return None
-    import torch
+    torch = _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch tensor" % name)
+    if _is(t, _DTYPES[32]):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError("%s must live on a HIP device" % name)
     if t.element_size() != 4 or t.dtype.is_floating_point:
@@ -187,24 +212,39 @@ def _wptr(t):
 
 
 def _stream(stream, like=None):
-    import torch
     if stream is None:
-        dev = like.device if like is not None else None
-        return torch.cuda.current_stream(dev).cuda_stream
+        torch = _torch()
+        if like is not None and _raw_stream is not None:
+            return _raw_stream(like.get_device())
+        return torch.cuda.current_stream(like.device if like is not None else None).cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
+def _moduli(q, limbs):
+    return [int(x) for x in (q if hasattr(q, "__len__") else [q])]
+
+
 def _qarr(q, limbs):
-    qs = [int(x) for x in (q if hasattr(q, "__len__") else [q])]
+    if type(q) is list and len(q) == limbs:
+        try:        # plain whole numbers in one conversion
+            return (ctypes.c_uint64 * limbs).from_buffer(array.array("Q", q))
+        except (TypeError, OverflowError):
+            pass
+    qs = _moduli(q, limbs)
     if len(qs) != limbs:
         raise ValueError("need %d moduli, got %d" % (limbs, len(qs)))
     return (ctypes.c_uint64 * limbs)(*qs)
 
 
 def _qarr32(q, limbs):
-    qs = [int(x) for x in (q if hasattr(q, "__len__") else [q])]
+    if type(q) is list and len(q) == limbs:
+        try:
+            return (ctypes.c_uint32 * limbs).from_buffer(array.array("I", q))
+        except (TypeError, OverflowError):
+            pass
+    qs = _moduli(q, limbs)
     if len(qs) != limbs:
         raise ValueError("need %d moduli, got %d" % (limbs, len(qs)))
     if any(x < 0 or x >= 1 << 32 for x in qs):

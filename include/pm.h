@@ -114,7 +114,9 @@ int pm_polymul_fused(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N
                      size_t polys_per_limb, const uint64_t *q, const uint64_t *psi_br,
                      const uint64_t *psi_inv_br, void *workspace, pm_stream_t stream);
 
-/* Workspace bytes pm_polymul and pm_polymul_fused need for this shape (0 if none). */
+/* Workspace bytes pm_polymul and pm_polymul_fused need for this shape (0 if
+ * none). It follows the plan of this very shape: a larger batch of the same N
+ * may be one pass and need less, so query every shape that is multiplied. */
 size_t pm_polymul_workspace_bytes(size_t N, size_t limbs, size_t polys_per_limb);
 
 /*

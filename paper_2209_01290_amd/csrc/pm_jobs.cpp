@@ -186,18 +186,23 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
   const int set = g_jobs_pipe.load();
   const bool pipelined = set != 0 && set != 1 && pipe_rows >= (set > 1 ? 1 : JOBS_PIPE_MIN_ROWS);
   const std::vector<uint32_t> order = table_order(L->jobs);
-  // Three-pass form: rows of up to 2^11 words and of 2^12 words are two launches. A
-  // batch that would need both takes rows of 2^12 words for every N >= 2^12
-  // instead: a short batch's launches each leave most of the GPU idle (five
-  // requests of N = 2^13..2^17: 23 + 59 us of rows as two launches), and a long one
-  // loses little to its tuned short rows.
-  bool rows11 = false, rows12 = false;
+  // Three-pass form: rows of up to 2^11, of 2^12, 2^13 and 2^14 words are a launch
+  // each. A batch whose tuned splits would need several of them for its sizes from
+  // 2^12 on takes rows of 2^12 words for all: a short batch's launches each leave
+  // most of the GPU idle (five requests of N = 2^13..2^17: 136 us with rows of
+  // 2^11 and 2^12 words, 117 with 2^12 alone), and a long one loses little to its
+  // tuned rows. Rows of 2^13 and 2^14 words (two and one workgroups to a CU)
+  // are used from as many rows as fill the GPU.
+  bool launch[PM_MAX_LOGC + 1] = {};
+  uint64_t long_rows = 0;
   for (const JobDev& J : L->jobs) {
     if (J.log2n < 12) continue;
-    const uint32_t logc = plan_for(OP_POLYMUL, J.log2n).logc;
-    rows11 |= logc <= 11;
-    rows12 |= logc == 12;
+    const PassPlan p = plan_for(OP_POLYMUL, J.log2n);
+    launch[std::max(p.logc, 11u)] = true;
+    if (p.logc > 12) long_rows += (uint64_t)J.count * p.R;
   }
+  const bool one_launch = launch[11] + launch[12] + launch[13] + launch[14] <= 1;
+  const bool tuned_rows = one_launch && (!(launch[13] || launch[14]) || long_rows >= (launch[13] ? 512 : 256));
   size_t ws = 0;
   std::vector<size_t> ws_job(njobs, 0);
   std::vector<uint32_t> pjobs;
@@ -210,7 +215,7 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
       pjobs.push_back((uint32_t)j);
     } else {
       const PassPlan p = plan_for(OP_POLYMUL, J.log2n);
-      J.logc = (rows11 && rows12 && J.log2n >= 12 && p.logc <= 11) ? 12 : p.logc;
+      J.logc = (J.log2n >= 12 && !tuned_rows) ? 12 : p.logc;
       J.logr = J.log2n - J.logc;
     }
     if (J.logr > 0 && J.nops == 2) {

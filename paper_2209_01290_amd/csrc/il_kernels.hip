@@ -12,12 +12,12 @@
 // Words between the passes of one transform are lazy (below LazyRule's H on the
 // way forward, below GIN on the way back); the last pass of a transform or a product
 // makes them canonical (LAST). The 1/N scaling is in the last stage of an
-// inverse transform (SCALE) or of the product's fused block.
+// inverse transform (SCALE) or of the product's middle.
 //
 //   IL_FWD  stages of Alg. 5 on one or two operands (A -> C, B -> D)
 //   IL_INV  stages of Alg. 6 (A -> C)
-//   IL_MUL  the last block of Alg. 5 on A and on B, the pointwise product and
-//           the first block of Alg. 6 (A, B -> C): Eq. 2's middle, fused
+//   IL_MUL  products of N <= 2^IL_MUL_MAXR, one block (A, B -> C); longer ones have
+//           their middle in il_rows.hip
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -114,8 +114,7 @@ static void il_launch_mode(const IlArgs& a, int mode, hipStream_t s) {
     else if (a.scale) il_launch<LOGR, KIND, IL_INV, true, true>(a, s);
     else il_launch<LOGR, KIND, IL_INV, true, false>(a, s);
   } else if constexpr (LOGR <= IL_MUL_MAXR) {
-    if (first) il_launch<LOGR, KIND, IL_MUL, true, true>(a, s);
-    else il_launch<LOGR, KIND, IL_MUL, false, true>(a, s);
+    il_launch<LOGR, KIND, IL_MUL, true, true>(a, s);
   }
 }
 
@@ -126,8 +125,8 @@ static void il_launch_kind(const IlArgs& a, int kind, int mode, hipStream_t s) {
 }
 
 hipError_t launch_il(int logr, int kind, int mode, const IlArgs& a, hipStream_t s) {
-  if (logr < 1 || logr > IL_MAXR || (mode == IL_MUL && logr > IL_MUL_MAXR)) return hipErrorInvalidValue;
-  if (a.s0 + (uint32_t)logr > a.log2n) return hipErrorInvalidValue;
+  if (logr < 1 || logr > IL_MAXR || a.s0 + (uint32_t)logr > a.log2n) return hipErrorInvalidValue;
+  if (mode == IL_MUL && (logr > IL_MUL_MAXR || (uint32_t)logr != a.log2n)) return hipErrorInvalidValue;
   switch (logr) {
     case 1: il_launch_kind<1>(a, kind, mode, s); break;
     case 2: il_launch_kind<2>(a, kind, mode, s); break;

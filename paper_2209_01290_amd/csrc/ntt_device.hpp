@@ -49,6 +49,9 @@ constexpr int row_geo(int logc, int ebx) { return logc | (ebx == 2 ? 32 : 0); }
 // bit 6: workgroups of at least 256 threads, several rows each (the job
 // tables' row kernel, one workgroup size for every row length)
 constexpr int ROW_GEO_SHARED = 64;
+// bit 7: the rows of a workgroup are the same row of several polynomials, so they
+// share its twiddles
+constexpr int ROW_GEO_SAME = 128;
 
 template <int GEO>
 struct RowGeom {
@@ -122,10 +125,10 @@ __device__ __forceinline__ uint32_t row_base(uint32_t t) {
   return ((t >> P) << (P + EB)) | (t & ((1u << P) - 1u));
 }
 
-// Round 0 of a row held by a whole workgroup: its twiddles are the same for
-// every thread (scalar loads, companions on the scalar unit).
+// Round 0 of a workgroup with one row (or one row of several polynomials): its
+// twiddles are the same for every thread (companions on the scalar unit).
 template <int GEO, int RHO>
-constexpr bool uniform_round() { return RHO == 0 && RowGeom<GEO>::ROWS == 1; }
+constexpr bool uniform_round() { return RHO == 0 && (RowGeom<GEO>::ROWS == 1 || (GEO & ROW_GEO_SAME)); }
 
 // Stages of round RHO when the TR smallest strides are left out.
 template <int GEO, int RHO, int TR>
@@ -343,22 +346,39 @@ __device__ __forceinline__ void lds_get(const W* lds, W (&x)[RowGeom<GEO>::E], u
   for (int j = 0; j < G::E; ++j) x[j] = b[lds_off<P>(j)];
 }
 
-template <int GEO, int RHO, typename W>
-__device__ __forceinline__ void gmem_get(const W* __restrict__ row, W (&x)[RowGeom<GEO>::E], uint32_t t) {
+// Where the words of a row are: next to each other, or (coefficient-major
+// batches) `step` words apart, `lane` words from a start that is the same for the
+// whole workgroup.
+struct Unit {
+  static constexpr uint32_t step = 1, lane = 0;
+  template <typename W>
+  __device__ __forceinline__ W* at(W* row, uint32_t i) const { return row + i; }
+};
+struct Strided {
+  uint32_t step, lane;
+  // word i of the row as a scalar address (opaque: the compiler would walk
+  // from word to word in vector registers and keep the addresses of the loads
+  // for the stores, 32 registers)
+  template <typename W>
+  __device__ __forceinline__ W* at(W* row, uint32_t i) const { return row + opaque_s(i * step); }
+};
+
+template <int GEO, int RHO, typename W, typename S>
+__device__ __forceinline__ void gmem_get(const W* __restrict__ row, W (&x)[RowGeom<GEO>::E], uint32_t t, S s) {
   using G = RowGeom<GEO>;
   constexpr int P = G::p(RHO);
-  const uint32_t tb = (G::NR > 1) ? row_base<P, G::EB>(t) : (t << G::EB);
+  const uint32_t tb = ((G::NR > 1) ? row_base<P, G::EB>(t) : (t << G::EB)) * s.step + s.lane;
 #pragma unroll
-  for (int j = 0; j < G::E; ++j) x[j] = (row + (j << P))[tb];
+  for (int j = 0; j < G::E; ++j) x[j] = s.at(row, j << P)[tb];
 }
 
-template <int GEO, int RHO, typename W>
-__device__ __forceinline__ void gmem_put(W* __restrict__ row, const W (&x)[RowGeom<GEO>::E], uint32_t t) {
+template <int GEO, int RHO, typename W, typename S>
+__device__ __forceinline__ void gmem_put(W* __restrict__ row, const W (&x)[RowGeom<GEO>::E], uint32_t t, S s) {
   using G = RowGeom<GEO>;
   constexpr int P = G::p(RHO);
-  const uint32_t tb = (G::NR > 1) ? row_base<P, G::EB>(t) : (t << G::EB);
+  const uint32_t tb = ((G::NR > 1) ? row_base<P, G::EB>(t) : (t << G::EB)) * s.step + s.lane;
 #pragma unroll
-  for (int j = 0; j < G::E; ++j) (row + (j << P))[tb] = x[j];
+  for (int j = 0; j < G::E; ++j) s.at(row, j << P)[tb] = x[j];
 }
 
 // Move registers from round FROM's layout to round TO's layout through LDS.
@@ -448,6 +468,7 @@ __device__ __forceinline__ void blk4_mul(W (&x)[RowGeom<GEO>::E], const W (&y)[R
     mul_mod_x4<KIND>(a, b, g, neg, M);
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[j + i] = a[i];
+    if (G::EB == 4) stage_fence();         // registers: one block at a time
   }
 }
 

@@ -22,16 +22,18 @@ constexpr bool product_in_blocks() {
 // more LDS exchange to round 0's layout makes them whole lines. Forward
 // transforms of N = 2^16 x 384: 217 -> 198 us for both passes, 182 with the
 // twiddles loaded ahead (RowTwRound).
+// Coefficient-major rows move whole lines in any layout.
 template <int GEO>
-constexpr bool exchange_io() { return RowGeom<GEO>::EB == 4 && RowGeom<GEO>::NR > 1; }
+constexpr bool exchange_io() { return RowGeom<GEO>::EB == 4 && RowGeom<GEO>::NR > 1 && !(GEO & ROW_GEO_SAME); }
 
 // Words of a split's row pass (R > 1) come from and go to a column pass in lazy
 // form: below H from the forward columns, below GIN to the inverse columns. With
 // R = 1 the input is canonical (which is below H too) and the output is made so
-// (single). lg = log2 N: the inverse scales by 1/N.
-template <int GEO, int KIND, int MODE, typename W, typename MT>
+// (single). lg = log2 N: the inverse scales by 1/N. st: the step between words.
+template <int GEO, int KIND, int MODE, typename W, typename MT, typename S = Unit>
 __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const W* tf, const W* ti, uint32_t Rr,
-                                         bool active, bool single, uint32_t lg, const MT& M, W* lds, uint32_t t) {
+                                         bool active, bool single, uint32_t lg, const MT& M, W* lds, uint32_t t,
+                                         S st = S{}) {
   using G = RowGeom<GEO>;
   using L = LazyRule<W, KIND>;
   constexpr int NX = MODE == ROW_MUL ? 2 : 1;
@@ -49,19 +51,19 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
     if constexpr (G::TW_LDS) tl = tw_lds_word(ti, t, Rr);
     const RowTw<GEO, 0, 1, W> tws(t, ti, Rr, table);
     if constexpr (exchange_io<GEO>()) {
-      if (active) gmem_get<GEO, 0>(A, x[0], t);
+      if (active) gmem_get<GEO, 0>(A, x[0], t, st);
       exchange<GEO, 0, G::NR - 1>(lds, x[0], t);
     } else {
-      if (active) gmem_get<GEO, G::NR - 1>(A, x[0], t);
+      if (active) gmem_get<GEO, G::NR - 1>(A, x[0], t, st);
     }
     if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, tl, t, M);
     inv_rounds<GEO, KIND, 0, Q1>(lds, x[0], t, tws, lg, M);
   } else {
     W tl = 0;
     if constexpr (G::TW_LDS) tl = tw_lds_word(tf, t, Rr);
-    if (active) gmem_get<GEO, 0>(A, x[0], t);
+    if (active) gmem_get<GEO, 0>(A, x[0], t, st);
     if constexpr (NX == 2) {
-      if (active) gmem_get<GEO, 0>(B, x[1], t);
+      if (active) gmem_get<GEO, 0>(B, x[1], t, st);
     }
     const RowTw<GEO, TR, NX, W> tws(t, tf, Rr, table);
     if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, tl, t, M);      // read after round 0's exchange
@@ -70,9 +72,9 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
       canon_all<KIND>(x[0], M);
       if constexpr (exchange_io<GEO>()) {
         exchange<GEO, G::NR - 1, 0>(lds, x[0], t);
-        if (active) gmem_put<GEO, 0>(Cout, x[0], t);
+        if (active) gmem_put<GEO, 0>(Cout, x[0], t, st);
       } else {
-        if (active) gmem_put<GEO, G::NR - 1>(Cout, x[0], t);
+        if (active) gmem_put<GEO, G::NR - 1>(Cout, x[0], t, st);
       }
       return;
     } else {
@@ -100,7 +102,7 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
     }
   }
   if (single) canon_all<KIND>(x[0], M);
-  if (active) gmem_put<GEO, 0>(Cout, x[0], t);
+  if (active) gmem_put<GEO, 0>(Cout, x[0], t, st);
 }
 
 // Register budget: 4 waves per SIMD (<= 128 VGPRs).

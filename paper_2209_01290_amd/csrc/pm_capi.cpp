@@ -622,13 +622,10 @@ int pm_polymul_fused_u32(const uint32_t* a, const uint32_t* b, uint32_t* c, size
 
 // ------------------------------------------------------ interleaved layout --
 // Batch [limb][N][polys]: coefficient j of polynomial p at j * polys + p.
-// A transform is a sequence of radix-2^r blocks of stages (il_kernels.hip),
-// each one launch over the whole batch; n stages split into the fewest
-// blocks of at most IL_MAXR stages, balanced, larger blocks first; the fused
-// middle block of the product holds two operands and takes at most
-// IL_MUL_MAXR stages (6 stages in it fit one wave per SIMD only: N = 2^12 x 999 as
-// 6 + 6 instead of 4 + 4 + 4 stages took 108 us against 103).
-
+// A transform is a sequence of radix-2^r blocks of stages (il_kernels.hip)
+// and one pass in LDS rows (il_rows.hip): the last stages of a forward transform, the
+// first of an inverse, the product's middle. n stages split into the fewest blocks
+// of at most IL_MAXR stages, balanced, larger blocks first.
 static int il_plan(unsigned n, int maxlast, int* sizes) {
   int np = (int)((n + IL_MAXR - 1) / IL_MAXR);
   for (;; ++np) {
@@ -636,6 +633,20 @@ static int il_plan(unsigned n, int maxlast, int* sizes) {
     for (int i = 0; i < np; ++i) sizes[i] = base + (i < rem ? 1 : 0);
     if (sizes[np - 1] <= maxlast) return np;
   }
+}
+
+// Passes of N = 2^n with an LDS row: sizes[0..n-2] register blocks, sizes[n-1]
+// the row. One pass up to 2^10; beyond, the row that measured best (N = 2^11..2^17,
+// batches of 2^22 and 2^25 words): radix-2^4 and 2^5 blocks and rows of 2^8 (four
+// workgroups to a CU) run nearest to the memory's rate, so a pass more, 4 + 4 + 8, beats
+// 6 + 10 for the transforms of 2^16 (275 us against 292 at 2^25 words), not for its
+// products, which would move three batches more (882 against 795).
+static int il_row_plan(unsigned n, bool mul, int* sizes) {
+  static const uint8_t rows[2][7] = {{7, 8, 8, 8, 9, 8, 8}, {7, 8, 8, 9, 9, 10, 8}};    // N = 2^11..2^17
+  const unsigned row = n <= (unsigned)IL_ROW_MAX ? n : rows[mul][n - IL_ROW_MAX - 1];
+  const int np = n > row ? il_plan(n - row, IL_MAXR, sizes) : 0;
+  sizes[np] = (int)row;
+  return np + 1;
 }
 
 static const char* il_name(int mode, int logr) {
@@ -654,6 +665,15 @@ static hipError_t run_il(int logr, int kind, int mode, const IlArgs& a, hipStrea
   return launch_il(logr, kind, mode, a, s);
 }
 
+// A pass in LDS rows of 2^n coefficients.
+static hipError_t run_il_row(int n, int kind, int mode, const IlArgs& a, hipStream_t s) {
+  static const char* const names[3][5] = {{"il_fwd_c6", "il_fwd_c7", "il_fwd_c8", "il_fwd_c9", "il_fwd_c10"},
+                                          {"il_inv_c6", "il_inv_c7", "il_inv_c8", "il_inv_c9", "il_inv_c10"},
+                                          {"il_mul_c6", "il_mul_c7", "il_mul_c8", "il_mul_c9", "il_mul_c10"}};
+  ProfScope ps(s, names[mode][n - IL_ROW_MIN]);
+  return launch_il_row(n, kind, mode, a, s);
+}
+
 static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, const uint64_t* q,
                          const uint64_t* tw, pm_stream_t stream, bool inv) {
   BatchT<uint64_t> b;
@@ -661,7 +681,10 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   if ((rc = check_batch(&b, N, limbs, polys, q))) return rc;
   if ((rc = check_ptr(x, "x")) || (rc = check_ptr(tw, inv ? "psi_inv_br" : "psi_br"))) return rc;
   int sz[32];
-  const int np = il_plan(b.log2n, IL_MAXR, sz);
+  // the last pass (the first one back) is an LDS row, which scales by 1/N; one register
+  // block does up to 2^6 (N = 2^6 x 65535: 22.0 us, as rows 26.0)
+  const bool row = b.log2n > (unsigned)IL_MAXR;
+  const int np = row ? il_row_plan(b.log2n, false, sz) : il_plan(b.log2n, IL_MAXR, sz);
   hipStream_t s = (hipStream_t)stream;
   if (validate_enabled() &&
       (rc = validate_batch<uint64_t>(b, {{x, "x"}}, {{tw, inv ? "psi_inv_br" : "psi_br"}}, s)))
@@ -669,18 +692,21 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   rc = for_chunks(b, [&](size_t l0, size_t nl, const LimbSet& ls) -> hipError_t {
     uint64_t* xs = x + l0 * polys * N;
     const uint64_t* t = tw + l0 * N;
-    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls, true};
+    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls, !row};
+    const auto run = [&](int k, int mode) {
+      return row && k == np - 1 ? run_il_row(sz[k], b.kind, mode, a, s) : run_il(sz[k], b.kind, mode, a, s);
+    };
     hipError_t e;
     if (!inv) {
       for (int k = 0; k < np; ++k) {
-        if ((e = run_il(sz[k], b.kind, IL_FWD, a, s)) != hipSuccess) return e;
+        if ((e = run(k, IL_FWD)) != hipSuccess) return e;
         a.s0 += (uint32_t)sz[k];
       }
     } else {
       a.s0 = b.log2n;
       for (int k = np - 1; k >= 0; --k) {
         a.s0 -= (uint32_t)sz[k];
-        if ((e = run_il(sz[k], b.kind, IL_INV, a, s)) != hipSuccess) return e;
+        if ((e = run(k, IL_INV)) != hipSuccess) return e;
       }
     }
     return hipSuccess;
@@ -702,6 +728,7 @@ int pm_ntt_inv_il(uint64_t* x, size_t N, size_t limbs, size_t polys_per_limb, co
 size_t pm_polymul_il_workspace_bytes(size_t N, size_t limbs, size_t polys_per_limb) {
   if (!is_pow2(N) || N < 2 || N > ((size_t)1 << PM_MAX_LOG2N)) return 0;
   int sz[32];
+  // (from N = 2^6 on, also where the product is one pass)
   return il_plan(log2u(N), IL_MUL_MAXR, sz) > 1 ? N * limbs * polys_per_limb * sizeof(uint64_t) : 0;
 }
 
@@ -716,12 +743,14 @@ int pm_polymul_il(const uint64_t* a, const uint64_t* b_, uint64_t* c, size_t N, 
       (rc = check_ptr(psi_br, "psi_br")) || (rc = check_ptr(psi_inv_br, "psi_inv_br")))
     return rc;
   int sz[32];
-  const int np = il_plan(b.log2n, IL_MUL_MAXR, sz);
+  const bool needs_ws = il_plan(b.log2n, IL_MUL_MAXR, sz) > 1;
+  const bool row = b.log2n >= (unsigned)IL_ROW_MIN;
+  const int np = row ? il_row_plan(b.log2n, true, sz) : il_plan(b.log2n, IL_MUL_MAXR, sz);
   const bool same = (a == b_);
   const uint64_t* A = a;
   const uint64_t* B = b_;
   if (c == B && c != A) std::swap(A, B);
-  if (np > 1 && !same && (rc = check_ptr(workspace, "workspace"))) return rc;
+  if (needs_ws && !same && (rc = check_ptr(workspace, "workspace"))) return rc;
   uint64_t* ws = (uint64_t*)workspace;
   hipStream_t s = (hipStream_t)stream;
   if (validate_enabled() &&
@@ -734,7 +763,7 @@ int pm_polymul_il(const uint64_t* a, const uint64_t* b_, uint64_t* c, size_t N, 
     hipError_t e;
     if (np == 1) {
       IlArgs m{A + base, B + base, c + base, nullptr, tf, ti, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls};
-      return run_il(sz[0], b.kind, IL_MUL, m, s);
+      return row ? run_il_row(sz[0], b.kind, IL_MUL, m, s) : run_il(sz[0], b.kind, IL_MUL, m, s);
     }
     uint64_t* wb = same ? c + base : ws + base;
     // forward blocks of a (-> c) and b (-> workspace), then in place
@@ -747,7 +776,7 @@ int pm_polymul_il(const uint64_t* a, const uint64_t* b_, uint64_t* c, size_t N, 
       f.s0 += (uint32_t)sz[k];
     }
     IlArgs m{c + base, wb, c + base, nullptr, tf, ti, b.log2n, f.s0, (uint32_t)polys, (uint32_t)nl, 1, &ls};
-    if ((e = run_il(sz[np - 1], b.kind, IL_MUL, m, s)) != hipSuccess) return e;
+    if ((e = run_il_row(sz[np - 1], b.kind, IL_MUL, m, s)) != hipSuccess) return e;
     IlArgs iv{c + base, nullptr, c + base, nullptr, tf, ti, b.log2n, f.s0, (uint32_t)polys, (uint32_t)nl, 1, &ls};
     for (int k = np - 2; k >= 0; --k) {
       iv.s0 -= (uint32_t)sz[k];

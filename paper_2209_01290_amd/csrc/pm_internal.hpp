@@ -98,6 +98,10 @@ struct IlArgs {
   bool scale = false;            // IL_INV of a transform: the block of stage 0 scales by 1/N
 };
 hipError_t launch_il(int logr, int kind, int mode, const IlArgs& a, hipStream_t s);
+// The last logc stages in LDS rows of 2^logc coefficients (il_rows.hip): IL_FWD, IL_INV
+// (scaled by 1/N) A -> C, IL_MUL (the product's middle) A, B -> C.
+constexpr int IL_ROW_MIN = 6, IL_ROW_MAX = 10;
+hipError_t launch_il_row(int logc, int kind, int mode, const IlArgs& a, hipStream_t s);
 
 // PM_VALIDATE scan (pm_validate.hip): flags_dev[l] = 1 if some word of limb
 // l's span of x (per_limb words of word_bytes each) is >= qs_dev[l].

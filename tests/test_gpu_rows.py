@@ -1,11 +1,48 @@
-"""Job tables whose tuned rows are of 2^13 or 2^14 words, on both sides of the row
+"""Row kernels where their lanes, rows and launches end: the coefficient-major
+layout's LDS rows (16 polynomials to a workgroup) around 16 polynomials, and job
+tables whose tuned rows are of 2^13 or 2^14 words, on both sides of the row
 counts from which those are used. Whole numbers against the oracle: no tolerance."""
+import numpy as np
 import pytest
 
-from gpu_helpers import first_mismatch, oracle_polymul, oracle_tables
+from gpu_helpers import first_mismatch, operands, oracle_ntt_fwd, oracle_ntt_inv, oracle_polymul, oracle_tables
 from paper_2209_01290_amd import synth
 
 pytestmark = pytest.mark.gpu
+
+
+# one pass (2^6..2^10: every row length), rows of 2^8 at both ends, of 2^9, of 2^10 below one and two blocks
+@pytest.mark.parametrize("bits", [60, 62])
+@pytest.mark.parametrize("log2n", [6, 7, 8, 9, 10, 11, 14, 15, 16, 17])
+@pytest.mark.parametrize("polys", [15, 16, 17, 33])
+def test_il_rows(log2n, polys, bits):
+    import torch
+    from paper_2209_01290_amd import lib as L
+    if log2n > 14 and polys > 17:
+        pytest.skip("the oracle's time")
+    N = 1 << log2n
+    qs = L.pm_ntt_primes(N, 2, bits)
+    prm = L.Params(N, 2, primes=qs)
+    fw, iv = oracle_tables(qs, N)
+    a, b = operands(N, qs, polys, request=1500 + log2n)
+    il = lambda x: np.ascontiguousarray(np.transpose(x, (0, 2, 1)))
+    da, db = L.to_device(il(a)), L.to_device(il(b))
+    # the words behind the result belong to somebody else
+    c = torch.full((2 * N * polys + 64,), -1, dtype=torch.int64, device="cuda")
+    ws = torch.empty(L.pm_polymul_il_workspace_bytes(N, 2, polys) // 8, dtype=torch.int64, device="cuda")
+    L.pm_polymul_il(da, db, c, N, 2, polys, qs, prm.psi_br, prm.psi_inv_br, ws)
+    got = L.to_host(c)
+    assert (got[2 * N * polys:] == np.uint64(2**64 - 1)).all()
+    got = np.transpose(got[: 2 * N * polys].reshape(2, N, polys), (0, 2, 1))
+    msg = first_mismatch(np.ascontiguousarray(got), oracle_polymul(a, b, qs, N, fw, iv))
+    assert msg is None, "N 2^%d x %d, %d bits: %s" % (log2n, polys, bits, msg)
+    x, y = da.clone(), da.clone()
+    L.pm_ntt_fwd_il(x, N, 2, polys, qs, prm.psi_br)
+    L.pm_ntt_inv_il(y, N, 2, polys, qs, prm.psi_inv_br)
+    for what, t, want in (("fwd", x, oracle_ntt_fwd(a, qs, fw)), ("inv", y, oracle_ntt_inv(a, qs, iv))):
+        got = np.transpose(L.to_host(t).reshape(2, N, polys), (0, 2, 1))
+        msg = first_mismatch(np.ascontiguousarray(got), want)
+        assert msg is None, "%s N 2^%d x %d, %d bits: %s" % (what, log2n, polys, bits, msg)
 
 
 # one tuned row length for all long sizes (2^13: 512 rows and more, 2^14: 256 and more), several, none

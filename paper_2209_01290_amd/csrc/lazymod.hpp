@@ -27,7 +27,7 @@
 // plus about 1.3 to 2 for reductions, against 32 and 40.8 with Alg. 4 and full
 // reductions in every butterfly. The product rows of N = 2^16 x 384 (6144 rows
 // of 2^12 words) went from 0.447 to 0.30 ms, 11,116 to 6,300 VALU instructions
-// a thread.
+// a thread. Under them the clock falls to 2.15 of 2.4 GHz (the power limit).
 //
 // Two rules per word type (LazyRule<W, KIND>); bounds are in sixteenths of q:
 //   64-bit, KIND_WIDE (34 <= len(q) <= 60): H = 16; words may grow over several
@@ -103,33 +103,23 @@ __device__ __forceinline__ uint64_t mulhi_exact(uint64_t a, uint64_t b) {
 }
 
 // a.b + c.d + e.f + g.h modulo 2^32 as four multiply-adds (the compiler would
-// narrow them to three multiplies and two additions more). w: the words of a
-// twiddle, in scalar registers if UNI.
-template <bool UNI>
+// narrow them to three multiplies and two additions more).
 __device__ __forceinline__ uint32_t cross4(uint64_t v, uint64_t w, uint64_t k, uint64_t nq) {
   uint64_t x, cc;
-  if (UNI)
-    asm("v_mad_u64_u32 %0, %1, %2, %3, 0\n\tv_mad_u64_u32 %0, %1, %4, %5, %0\n\t"
-        "v_mad_u64_u32 %0, %1, %6, %7, %0\n\tv_mad_u64_u32 %0, %1, %8, %9, %0"
-        : "=&v"(x), "=&s"(cc)
-        : "v"(lo32(v)), "s"(hi32(w)), "v"(hi32(v)), "s"(lo32(w)), "v"(lo32(k)), "s"(hi32(nq)), "v"(hi32(k)),
-          "s"(lo32(nq)));
-  else
-    asm("v_mad_u64_u32 %0, %1, %2, %3, 0\n\tv_mad_u64_u32 %0, %1, %4, %5, %0\n\t"
-        "v_mad_u64_u32 %0, %1, %6, %7, %0\n\tv_mad_u64_u32 %0, %1, %8, %9, %0"
-        : "=&v"(x), "=&s"(cc)
-        : "v"(lo32(v)), "v"(hi32(w)), "v"(hi32(v)), "v"(lo32(w)), "v"(lo32(k)), "s"(hi32(nq)), "v"(hi32(k)),
-          "s"(lo32(nq)));
+  asm("v_mad_u64_u32 %0, %1, %2, %3, 0\n\tv_mad_u64_u32 %0, %1, %4, %5, %0\n\t"
+      "v_mad_u64_u32 %0, %1, %6, %7, %0\n\tv_mad_u64_u32 %0, %1, %8, %9, %0"
+      : "=&v"(x), "=&s"(cc)
+      : "v"(lo32(v)), "v"(hi32(w)), "v"(hi32(v)), "v"(lo32(w)), "v"(lo32(k)), "s"(hi32(nq)), "v"(hi32(k)),
+        "s"(lo32(nq)));
   return lo32(x);
 }
 
 // acc + v w - k q modulo 2^64
-template <bool UNI>
 __device__ __forceinline__ uint64_t fma_q(uint64_t v, uint64_t w, uint64_t k, uint64_t acc, const Mod& M) {
   const uint64_t nq = neg_q(M);
   uint64_t s = (uint64_t)lo32(v) * lo32(w) + acc;
   s = (uint64_t)lo32(k) * lo32(nq) + s;
-  return add_high(s, cross4<UNI>(v, w, k, nq));
+  return add_high(s, cross4(v, w, k, nq));
 }
 
 // Companions. With ws = w 2^(64-m) and 2^(m+64)/q = 2^64 + M.ml (+ fraction):
@@ -143,11 +133,16 @@ __device__ __forceinline__ uint64_t companion(uint64_t w, bool uni, const Mod& M
   return p + ((0 - p * M.q) >= M.q ? 1 : 0);      // remainder w 2^64 - p q < 2q
 }
 
-// acc + v t.w mod q: the product is below rmax(V) for v < V q.
-template <int KIND, bool UNI = false>
-__device__ __forceinline__ uint64_t mul_tw(uint64_t v, const Tw<uint64_t>& t, uint64_t acc, const Mod& M) {
+// u + v t.w mod q (mul_add_tw) and v t.w mod q: the product is below rmax(V) for v < V q.
+template <int KIND>
+__device__ __forceinline__ uint64_t mul_add_tw(uint64_t& u, uint64_t v, const Tw<uint64_t>& t, const Mod& M) {
   const uint64_t k = KIND == KIND_WIDE ? mulhi_low3(v, t.p) : mulhi_exact(v, t.p);
-  return fma_q<UNI>(v, t.w, k, acc, M);
+  return fma_q(v, t.w, k, u, M);
+}
+template <int KIND>
+__device__ __forceinline__ uint64_t mul_tw(uint64_t v, const Tw<uint64_t>& t, const Mod& M) {
+  uint64_t zero = 0;
+  return mul_add_tw<KIND>(zero, v, t, M);
 }
 
 // x < H q -> below 2q. KIND_WIDE: k = hi32(x1 c) with x1 = x >> 32 and
@@ -209,9 +204,30 @@ __device__ __forceinline__ uint32_t companion(uint32_t w, bool, const Mod32& M) 
   return p + ((0u - p * M.q) >= M.q ? 1u : 0u);
 }
 
-template <int KIND, bool UNI = false>
-__device__ __forceinline__ uint32_t mul_tw(uint32_t v, const Tw<uint32_t>& t, uint32_t acc, const Mod32& M) {
-  return acc + v * t.w - __umulhi(v, t.p) * M.q;
+// v w - k q modulo 2^32 as two multiply-adds, which take 64-bit addends: only the
+// low words matter, so the high ones are left as they come (opaque, or the compiler
+// makes four 32-bit instructions of the two). The product rows of 2^12 words:
+// 727 -> 679 in instructions weighted by issue rate, with mul_mod_x4's; products of
+// N = 2^16 x 768: 438 -> 409 us.
+__device__ __forceinline__ uint32_t sub_kq(uint64_t s, uint32_t v, const Tw<uint32_t>& t, const Mod32& M) {
+  s = (uint64_t)__umulhi(v, t.p) * opaque_s(0u - M.q) + s;
+  asm("" : "+v"(s));
+  return lo32(s);
+}
+template <int KIND>
+__device__ __forceinline__ uint32_t mul_tw(uint32_t v, const Tw<uint32_t>& t, const Mod32& M) {
+  return sub_kq((uint64_t)v * t.w, v, t, M);
+}
+template <int KIND>
+__device__ __forceinline__ uint32_t mul_add_tw(uint32_t& u, uint32_t v, const Tw<uint32_t>& t, const Mod32& M) {
+  uint32_t h;
+  asm volatile("" : "=v"(h));       // any word
+  uint64_t p = pack64(u, h);
+  asm("" : "+v"(p));
+  u = lo32(p);
+  uint64_t s = (uint64_t)v * t.w + p;
+  asm("" : "+v"(s));
+  return sub_kq(s, v, t, M);
 }
 
 template <int KIND>
@@ -254,7 +270,7 @@ constexpr int ct_bound(int b, int stages, bool uni) {
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void ct_lazy(W& u, W& v, const Tw<W>& t, bool red, int k, const MT& M) {
   if (red) u = red2<KIND>(u, M);
-  const W s = mul_tw<KIND>(v, t, u, M);
+  const W s = mul_add_tw<KIND>(u, v, t, M);
   v = ((u << 1) + mult_q<W>(k, M)) - s;
   u = s;
 }
@@ -264,7 +280,7 @@ template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void gs_lazy(W& u, W& v, const Tw<W>& t, int k, const MT& M) {
   const W d = u + mult_q<W>(k, M) - v;
   u = u + v;
-  v = mul_tw<KIND>(d, t, (W)0, M);
+  v = mul_tw<KIND>(d, t, M);
 }
 
 // The last GS stage of a transform with the scaling by N^-1 folded in:
@@ -272,8 +288,8 @@ __device__ __forceinline__ void gs_lazy(W& u, W& v, const Tw<W>& t, int k, const
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void gs_lazy_scaled(W& u, W& v, const Tw<W>& c, const Tw<W>& cw, int k, const MT& M) {
   const W d = u + mult_q<W>(k, M) - v;
-  u = mul_tw<KIND>((W)(u + v), c, (W)0, M);
-  v = mul_tw<KIND>(d, cw, (W)0, M);
+  u = mul_tw<KIND>((W)(u + v), c, M);
+  v = mul_tw<KIND>(d, cw, M);
 }
 
 // 2^-lg mod q for 2^lg | q - 1
@@ -350,7 +366,7 @@ __device__ __forceinline__ void mul_mod_x4(uint64_t (&a)[4], const uint64_t (&b)
     A[i] = limbs31(red2<KIND>(a[i], M));
     B[i] = limbs31(bi);
     if (i) {
-      const uint64_t z = mul_tw<KIND>(bi, g, (uint64_t)0, M);        // < 3.5 q
+      const uint64_t z = mul_tw<KIND>(bi, g, M);        // < 3.5 q
       Z[i] = limbs31(red2<KIND>(neg ? mult_q<uint64_t>(4, M) - z : z, M));
     }
   }
@@ -369,19 +385,23 @@ __device__ __forceinline__ void mul_mod_x4(uint64_t (&a)[4], const uint64_t (&b)
   }
 }
 
-// 32-bit words: canonical operands, S < 4 q^2 < 2^62; c = S >> m < 4q, the quotient
-// c + hi32(c ml) falls short of S/q by less than 2 + 1 + 1, so r < 4q < 2^32.
+// 32-bit words: operands below 2q, S < 16 q^2 < 2^64. With R = 2^32 mod q the sum
+// hi32(S) R + lo32(S) < 2^32 q is S modulo q; c = it >> m < 2^32, and the quotient
+// c + hi32(c ml) falls short by less than 2 + 1 + 1, so r < 4q < 2^32. (Canonical
+// operands would need no second sum: four multiply-adds against eleven conditional
+// subtractions, 94 -> 80 instructions a block.)
 template <int KIND>
 __device__ __forceinline__ void mul_mod_x4(uint32_t (&a)[4], const uint32_t (&b)[4], const Tw<uint32_t>& g, bool neg,
                                            const Mod32& M) {
+  const uint32_t R = opaque_s(0u - (uint32_t)((((uint64_t)1 << 32) | M.ml) >> (M.s + 2)) * M.q);
   uint32_t A[4], B[4], Z[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    A[i] = canon<KIND>(a[i], M);
-    B[i] = canon<KIND>(b[i], M);
+    A[i] = red2<KIND>(a[i], M);
+    B[i] = red2<KIND>(b[i], M);
     if (i) {
-      const uint32_t z = mul_tw<KIND>(B[i], g, 0u, M);               // < 2q
-      Z[i] = csub1(neg ? 2 * M.q - z : z, M);                         // <= q
+      const uint32_t z = mul_tw<KIND>(B[i], g, M);               // < 2q
+      Z[i] = neg ? 2 * M.q - z : z;                                   // <= 2q
     }
   }
 #pragma unroll
@@ -389,6 +409,7 @@ __device__ __forceinline__ void mul_mod_x4(uint32_t (&a)[4], const uint32_t (&b)
     uint64_t s = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) s = (uint64_t)A[i] * (i <= n ? B[n - i] : Z[4 + n - i]) + s;
+    s = (uint64_t)(uint32_t)(s >> 32) * R + (uint32_t)s;
     const uint32_t c = __builtin_amdgcn_alignbit((uint32_t)(s >> 32), (uint32_t)s, M.s + 2);
     const uint32_t k = c + __umulhi(c, M.ml);
     a[n] = red2<KIND>((uint32_t)s - k * M.q, M);

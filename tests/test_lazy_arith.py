@@ -61,12 +61,6 @@ def test_bounds_64(m):
             assert 0 <= 2 * (a * b - _mulhi_low3(cc, mu) * q) < 9 * q
 
 
-def _x4(a, b, g, q):
-    """Coefficients of a b mod (x^4 - g), as whole numbers (sums of four products each)."""
-    z = [g * v % q for v in b]
-    return [sum(a[i] * (b[n - i] if i <= n else z[4 + n - i]) for i in range(4)) for n in range(4)]
-
-
 @pytest.mark.parametrize("m", [34, 35, 47, 59, 60])
 def test_block_product_64(m):
     """Sums of four products of words below 2q: the limb sums fit 64 bits and the
@@ -92,19 +86,23 @@ def test_block_product_64(m):
             assert k < 1 << 64 and 0 <= S - k * q < 6 * q
 
 
-@pytest.mark.parametrize("m", [3, 17, 29, 30])
+@pytest.mark.parametrize("m", [4, 17, 29, 30])
 def test_block_product_32(m):
     rnd = random.Random(m)
     for q in {(1 << m) - 1, (1 << (m - 1)) + 1, rnd.randrange(1 << (m - 1), 1 << m) | 1}:
         ml = ((1 << (m + 32)) // q) - (1 << 32)
-        for _ in range(100):
-            a = [_edge(rnd, q) for _ in range(4)]
-            b = [_edge(rnd, q) for _ in range(4)]
-            for S in _x4(a, b, _edge(rnd, q), q):
-                c = S >> m
-                assert S < 1 << 64 and c < 1 << 32
-                k = c + _hi(c * ml)
-                assert k < 1 << 32 and 0 <= S - k * q < 4 * q < 1 << 32
+        R = (-(((1 << 32) + ml) >> m) * q) % (1 << 32)
+        assert R == (1 << 32) % q
+        for i in range(200):
+            a = [_edge(rnd, 2 * q) if i else 2 * q - 1 for _ in range(4)]
+            b = [_edge(rnd, 2 * q + 1) if i else 2 * q for _ in range(4)]     # 2q: a negated zero
+            S = sum(x * y for x, y in zip(a, b))
+            assert S < 1 << 64
+            s = _hi(S) * R + _lo(S)
+            c = s >> m
+            assert s % q == S % q and s < 1 << 64 and c < 1 << 32
+            k = c + _hi(c * ml)
+            assert k < 1 << 32 and 0 <= s - k * q < 4 * q < 1 << 32
 
 
 @pytest.mark.parametrize("bits,m", [(64, 2), (64, 33), (64, 61), (64, 62), (32, 3), (32, 29), (32, 30)])

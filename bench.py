@@ -47,31 +47,28 @@ CLOCK_MHZ = 2400.0
 PEAK_VALU_TOPS = 256 * 4 * 16 * CLOCK_MHZ * 1e6 / 1e12
 PEAK_HBM_GBPS = 8000.0
 # VALU instructions per unit of the method's work, counted in the ISA of
-# register-resident loops over the device arithmetic (modarith.hpp). A GS
-# butterfly takes its twiddle halved (38 instructions) and each twiddle is
-# halved once for the butterflies that share it (6 instructions; 15 twiddles
-# per 32 butterflies in the radix-16 rounds).
-TW_PER_GS = 15 / 32
-OPS_CT, OPS_GS, OPS_MUL = 32, 38 + 6 * TW_PER_GS, 22
+# register-resident loops over the device arithmetic (lazymod.hpp): a CT and a GS
+# butterfly, and one word of the product of residues modulo x^4 - g, which
+# takes the place of the two smallest strides of the three transforms. Reductions
+# between stages, the twiddles' companions and addresses are not counted.
+OPS_CT, OPS_GS, OPS_MUL = 14, 15, 65
+MUL_STAGES = 2
 
 
 # The same counts by instruction class: each class is priced by the probe
-# instruction that stands for it (pm_probe_valu's measured issue rates), which
+# instruction that stands for it (pm_probe_valu's measured issue rates; two-operand
+# additions and logic as v_xor_b32, 64-bit shifts as v_lshl_add_u64), which
 # gives the VALU-bound time of a launch for this instruction mix.
 MIX = {
-    "ct": {"v_mad_u64_u32": 8, "v_mul_hi_u32": 1, "v_mul_lo_u32": 2, "v_add3_u32": 1, "v_alignbit_b32": 2,
-           "v_lshl_add_u64": 2, "v_sub_co_u32": 15, "v_mov_b32": 1},
-    "gs": {"v_mad_u64_u32": 8, "v_mul_hi_u32": 1, "v_mul_lo_u32": 2, "v_add3_u32": 2 + TW_PER_GS,
-           "v_alignbit_b32": 2, "v_lshl_add_u64": 4 + 2 * TW_PER_GS, "v_sub_co_u32": 15,
-           "v_xor_b32": 3 + 3 * TW_PER_GS, "v_mov_b32": 1},
-    "mul": {"v_mad_u64_u32": 8, "v_mul_hi_u32": 1, "v_mul_lo_u32": 2, "v_add3_u32": 1, "v_alignbit_b32": 2,
-            "v_sub_co_u32": 7, "v_mov_b32": 1},
+    "ct": {"v_mad_u64_u32": 8, "v_mul_hi_u32": 2, "v_xor_b32": 1, "v_lshl_add_u64": 1, "v_sub_co_u32": 2},
+    "gs": {"v_mad_u64_u32": 8, "v_mul_hi_u32": 2, "v_xor_b32": 1, "v_lshl_add_u64": 2, "v_sub_co_u32": 2},
+    "mul": {"v_mad_u64_u32": 29.75, "v_mul_hi_u32": 6.25, "v_mul_lo_u32": 3.75, "v_alignbit_b32": 6.75,
+            "v_xor_b32": 11.25, "v_lshl_add_u64": 5.25, "v_add3_u32": 1, "v_mov_b32": 1},
 }
 assert all(abs(sum(MIX[u].values()) - o) < 1e-9 for u, o in (("ct", OPS_CT), ("gs", OPS_GS), ("mul", OPS_MUL)))
 
-# The same counts for 32-bit words (modarith32.hpp), moduli with m <= 29 /
-# m = 30 (one more shift per modular product).
-OPS32 = {29: (14, 17 + 4 * TW_PER_GS, 7), 30: (15, 18 + 4 * TW_PER_GS, 8)}
+# The same counts for 32-bit words (any modulus below 2^30).
+OPS32 = (5, 6, 18.25)
 
 
 def alg_ops(name: str, N: int, limbs: int, polys: int, ops=(OPS_CT, OPS_GS, OPS_MUL),
@@ -88,6 +85,7 @@ def alg_ops(name: str, N: int, limbs: int, polys: int, ops=(OPS_CT, OPS_GS, OPS_
         rows = limbs * polys * (N // C)
         half = (C // 2) * int(logc)            # butterflies of one row transform
         if mode == "mul":
+            half -= (C // 2) * MUL_STAGES
             per = 2 * half * ct + C * mul + half * gs
         elif mode == "fwd":
             per = half * ct
@@ -124,7 +122,7 @@ def mix_ceiling(name: str, N: int, limbs: int, polys: int, rates: dict) -> float
 
 # The sources the reported kernels are compiled from: the counter summary
 # stays valid while these are unchanged (host-only files do not matter).
-ROW_KERNEL_SOURCES = ("modarith.hpp", "modarith32.hpp", "ntt_device.hpp", "ntt_row.hpp", "pm_internal.hpp",
+ROW_KERNEL_SOURCES = ("modarith.hpp", "modarith32.hpp", "lazymod.hpp", "ntt_device.hpp", "ntt_row.hpp", "pm_internal.hpp",
                       "row_kernel.inc", "row_12.hip", "row_fixed.inc", "row_12r.hip", "pm_kernels.hip",
                       "pipe_kernels.hip", "pm_pipe.hpp")
 
@@ -322,7 +320,7 @@ def mixed_batch(torch, lib, dev, launches=5):
     ms_plain = e0.elapsed_time(e1)
     # algorithmic VALU work of the batch (the per-unit counts of the uniform
     # step): butterflies of the three transforms and the pointwise products
-    ops = sum(L * (1 << n) * (n * (OPS_CT + OPS_GS / 2.0) + OPS_MUL) for n, L in reqs)
+    ops = sum(L * (1 << n) * ((n - MUL_STAGES) * (OPS_CT + OPS_GS / 2.0) + OPS_MUL) for n, L in reqs)
     pipe_ms = sum(v[1] for k, v in kern.items() if k == "jobs_pipe_mul_c12") / 2.0
     return {"what": "512 requests, N uniform on 2^12..2^17, 1..48 limbs (%d limb-products), one plan "
                     "(HIP graph) launch per batch" % mb.products,
@@ -474,7 +472,7 @@ def _graph_call_us(torch, fn, calls=20, reps=10):
 
 
 def words32(torch, lib, dev, steps=20):
-    """The 32-bit word path (moduli up to 30 bits, Alg. 4 with beta = 32):
+    """The 32-bit word path (moduli up to 30 bits):
     single-transform latency at N = 2^14 and 2^16 beside 62-bit moduli on
     64-bit words (the rows of the paper's comparison table in Sec. VII; device
     time per call from HIP-graph replays, and the time per call when each is
@@ -542,9 +540,9 @@ def words32(torch, lib, dev, steps=20):
     def step_ops(name):
         # algorithmic ops of one step over all 96 limbs
         if name.startswith("pipe32_mul"):
-            return sum(alg_ops(k, N, L32, P, OPS32[30])
+            return sum(alg_ops(k, N, L32, P, OPS32)
                        for k in ("row32_mul_c12", "col32_fwd_r%d" % logr, "col32_inv_r%d" % logr))
-        return alg_ops(name, N, L32, P, OPS32[30])
+        return alg_ops(name, N, L32, P, OPS32)
 
     dom = max(k32.items(), key=lambda kv: kv[1][1])[0]
     achieved = step_ops(dom) * steps / (k32[dom][1] / 1e3) / 1e12
@@ -552,7 +550,7 @@ def words32(torch, lib, dev, steps=20):
     achieved3 = step_ops(row3) * steps / (k3[row3][1] / 1e3) / 1e12
     x = da.clone()
     ntt_us = _median_call_us(torch, stream, lambda: lib.pm_ntt_fwd_u32(x, N, L32, P, prm.q, prm.psi_br), 20)
-    return {"what": "32-bit words, moduli < 2^30 (Alg. 4, beta = 32)",
+    return {"what": "32-bit words, moduli < 2^30",
             "single_transform_latency": lat,
             "polymul_96x30bit_limbs": {
                 "limbs": L32, "polys_per_limb": P, "ms_per_step": round(ms, 4),
@@ -563,7 +561,7 @@ def words32(torch, lib, dev, steps=20):
                 "roofline": {"bound": "alu", "kernel": dom, "achieved": round(achieved, 3),
                              "peak": round(PEAK_VALU_TOPS, 3), "unit": "TOP/s",
                              "frac": round(achieved / PEAK_VALU_TOPS, 4),
-                             "ops_per_unit": {"ct": OPS32[30][0], "gs": OPS32[30][1], "mul": OPS32[30][2]}},
+                             "ops_per_unit": {"ct": OPS32[0], "gs": OPS32[1], "mul": OPS32[2]}},
                 "timing": "median of 4 alternating blocks of 10 steps, pipelined and three-pass",
                 "three_pass": {"ms_per_step": round(ms3, 4),
                                "kernels_avg_ms": {k: round(v[1] / v[0], 4) for k, v in sorted(k3.items())},
@@ -874,7 +872,7 @@ def main():
         out["fused"] = {"value": round(products / f_ms * 1e3, 1), "unit": "polymul/s",
                         "ms_per_step": round(f_ms, 4), "eq2_ms_per_step_alternating": round(q_ms, 4),
                         "fused_over_eq2": round(q_ms / f_ms, 4),
-                        "what": "pm_polymul_fused (Alg. 8: truncated NTTs + Karatsuba-fused Hadamard), "
+                        "what": "pm_polymul_fused (Alg. 8; two stages left out, as in the Eq. 2 step's rows), "
                                 "median of 4 blocks of 10 steps alternating with the Eq. 2 step",
                         "kernels_avg_ms": {k: round(v[1] / v[0], 4) for k, v in sorted(fk.items())}}
         # stagewise: one launch per NTT stage, whole batch per launch

@@ -308,7 +308,8 @@ size_t pm_tune_get_small_limit(int op, unsigned log2n);
  * group's products (limb-major) into G chunks and run G + 2 launches; launch
  * j does the row pass of chunk j-1, the forward column pass of chunk j and
  * the inverse column pass of chunk j-2, so that the memory-bound column work
- * overlaps the VALU-bound rows. chunks = -1 (the default) pipelines a launch
+ * runs beside the VALU-bound rows (1 to 2 % faster than three passes where it
+ * is; the rows are limited by power). chunks = -1 (the default) pipelines a launch
  * group over 2 chunks when its row pass has at least 2048 rows (never at
  * N = 2^17; unless tuned: pm_tune_set_pipeline_rows), i.e. from 256 / 128
  * products at N = 2^15 / 2^16:

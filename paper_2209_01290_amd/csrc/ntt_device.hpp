@@ -442,7 +442,7 @@ __device__ __forceinline__ void inv_rounds(W* lds, W (&x)[RowGeom<GEO>::E], uint
 // thread has used two stages before. 16 plain products and four reductions
 // replace two stages of three transforms, four reduced products and the twelve
 // twiddles a thread of 16 words reads for the last two stages: for the
-// rows of 2^12 words 6,310 -> 5,560 VALU instructions a thread.
+// rows of 2^12 words 6,310 -> 6,010 VALU instructions a thread (260 a block).
 // x = x y for the E consecutive words of a thread (last round's layout), rows of
 // at least 8 words; products below LazyRule::B4.
 template <int GEO, typename W>

@@ -5,8 +5,8 @@
 //
 // Two forms:
 //   * three-pass: each pass is one launch over the work items of all jobs
-//     (three to six launches whatever the mix: rows up to 2^11, of 2^12 and tuned
-//     long rows go to separate row kernels);
+//     (three or four launches whatever the mix: rows of up to 2^11 words are one,
+//     those of 2^12, 2^13 or 2^14 words, of which a batch uses one kind, another);
 //   * software-pipelined (batches whose jobs of N >= 2^12 hold at least
 //     JOBS_PIPE_MIN_ROWS rows of 2^12 words): those jobs take rows of 2^12
 //     words, their products are split into G chunks of about equal work, and

@@ -36,8 +36,8 @@ bool valid_small_split(unsigned log2n, unsigned logc) {
 
 uint32_t default_logc(int op, unsigned log2n) {
   // Rows of 2^12 words (32 KiB of LDS, 256 threads) keep four workgroups per
-  // CU; a whole polynomial up to 2^13 words (fused product) or 2^14 words
-  // (single transform) fits one workgroup's LDS.
+  // CU; a whole polynomial up to 2^13 words (products) or 2^14 words
+  // (transforms) is one row.
   const unsigned single_max = (op == OP_POLYMUL) ? 13 : 14;
   if (log2n <= single_max) return log2n;
   return 12;
@@ -84,8 +84,9 @@ void plan_pipe_set(int chunks) { g_pipe.store(chunks < 0 ? -1 : chunks); }
 int plan_pipe() { return g_pipe.load(); }
 
 namespace {
-// built-in thresholds, from a sweep of batch sizes on MI355X (2^15..2^17):
-// at 2^17 the three passes are the faster form at every batch size
+// built-in thresholds, for a library without a tuning database: two chunks are within
+// 2 % of three passes on either side of them (2^16 x 128: 198 against 192 us, x 384:
+// 481 against 486; 2^17 x 480: 1251 against 1261)
 constexpr size_t PIPE_MIN_ROWS_DEFAULT[3] = {2048, 2048, SIZE_MAX};
 std::atomic<size_t> g_pipe_rows[3] = {{0}, {0}, {0}};
 }  // namespace

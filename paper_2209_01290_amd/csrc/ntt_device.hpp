@@ -197,7 +197,9 @@ struct TwLds {
   __device__ __forceinline__ Tw<W> get(int jb, int g, const MT&) const { return p[(r16 << (3 - jb)) + g - 16]; }
 };
 // The word of slot t (slots from 240 on are not read), and its entry with the
-// companion; every thread writes one, so that no branch is needed.
+// companion; every thread writes one, so that no branch is needed. One companion
+// a thread costs nothing as the closer one of tw_uni, and its bound saves a reduction
+// of half the words in every fourth stage.
 template <typename W>
 __device__ __forceinline__ W tw_lds_word(const W* __restrict__ tw, uint32_t t, uint32_t Rr) {
   const uint32_t j = t < 240 ? t + 16 : 16, s = 27 - __builtin_clz(j);      // floor(log2 j) - 4
@@ -205,7 +207,7 @@ __device__ __forceinline__ W tw_lds_word(const W* __restrict__ tw, uint32_t t, u
 }
 template <int KIND, typename W, typename MT>
 __device__ __forceinline__ void tw_lds_put(Tw<W>* table, W w, uint32_t t, const MT& M) {
-  table[t] = tw_vec<KIND>(w, M);
+  table[t] = tw_uni<KIND>(w, M);
 }
 
 // Forward (CT) stages pairing register bits [JLO, JHI), largest first, on the
@@ -273,7 +275,8 @@ template <int GEO, int RHO, int TR>
 struct Round {
   using G = RowGeom<GEO>;
   static constexpr int P = G::p(RHO), JHI = G::hi(RHO) - P, JLO = JHI - round_stages<GEO, RHO, TR>();
-  static constexpr bool UNI = uniform_round<GEO, RHO>();
+  // companions short by less than two (tw_uni): the scalar unit's and the table's
+  static constexpr bool UNI = uniform_round<GEO, RHO>() || (G::TW_LDS && RHO == 1);
   template <typename TW, typename W>
   static __device__ __forceinline__ TW twiddles(uint32_t t, const W* __restrict__ tw, uint32_t Rr) {
     return TW(tw, round_block<GEO>(t, Rr, P), JLO, JHI);
@@ -558,6 +561,16 @@ template <int LOGR, int KIND, typename W, typename MT>
 __device__ __forceinline__ void col_inv(W (&x)[1 << LOGR], const W* __restrict__ tw, const MT& M) {
   blk_inv<LOGR, KIND, true, LazyRule<W, KIND>::GIN, false>(x, tw, 1, 0, M);
   canon_all<KIND>(x, M);
+}
+
+// Bound on the words a forward column pass of 2^LOGR rows leaves (LOGR = 0: none,
+// canonical words), in whichever of the forms here it ran.
+template <int LOGR, int KIND, typename W>
+constexpr int col_bound() {
+  constexpr int one = ct_bound<W, KIND>(Q1, LOGR, true);
+  if (LOGR != 5) return one;
+  constexpr int pair = ct_bound<W, KIND>(ct_stage<W, KIND>(Q1, true).out, 4, false);
+  return one > pair ? one : pair;
 }
 
 // Exchange between the two halves of a wave (v_permlane32_swap, gfx950).

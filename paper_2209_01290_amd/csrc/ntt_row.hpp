@@ -30,13 +30,16 @@ constexpr bool exchange_io() { return RowGeom<GEO>::EB == 4 && RowGeom<GEO>::NR 
 // form: below H from the forward columns, below GIN to the inverse columns. With
 // R = 1 the input is canonical (which is below H too) and the output is made so
 // (single). lg = log2 N: the inverse scales by 1/N. st: the step between words.
-template <int GEO, int KIND, int MODE, typename W, typename MT, typename S = Unit>
-__device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const W* tf, const W* ti, uint32_t Rr,
+// BIN: the forward rows' bound where it is known to be lower (col_bound), which saves
+// the reductions of one stage in ten.
+template <int GEO, int KIND, int MODE, int BIN = 0, typename W, typename MT, typename S = Unit>
+__device__ __forceinline__ void row_task(const W* A, const W* Bp, W* Cout, const W* tf, const W* ti, uint32_t Rr,
                                          bool active, bool single, uint32_t lg, const MT& M, W* lds, uint32_t t,
                                          S st = S{}) {
   using G = RowGeom<GEO>;
   using L = LazyRule<W, KIND>;
   constexpr int NX = MODE == ROW_MUL ? 2 : 1;
+  constexpr int B = BIN ? BIN : L::H;
   // the product leaves out the two smallest strides of its three transforms
   // where it can (blk4_mul): not for moduli beyond 60 bits on 64-bit words
   constexpr int TR = (MODE == ROW_MUL || MODE == ROW_SQR) && product_in_blocks<GEO, KIND, W>() ? 2 : 0;
@@ -63,12 +66,12 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
     if constexpr (G::TW_LDS) tl = tw_lds_word(tf, t, Rr);
     if (active) gmem_get<GEO, 0>(A, x[0], t, st);
     if constexpr (NX == 2) {
-      if (active) gmem_get<GEO, 0>(B, x[1], t, st);
+      if (active) gmem_get<GEO, 0>(Bp, x[1], t, st);
     }
     const RowTw<GEO, TR, NX, W> tws(t, tf, Rr, table);
     if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, tl, t, M);      // read after round 0's exchange
     if constexpr (MODE == ROW_FWD) {
-      fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
+      fwd_rounds<GEO, KIND, TR, B>(lds, x, t, tws, M);
       canon_all<KIND>(x[0], M);
       if constexpr (exchange_io<GEO>()) {
         exchange<GEO, G::NR - 1, 0>(lds, x[0], t);
@@ -81,7 +84,7 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
       const RowTw<GEO, TR, 1, W> iws(t, ti, Rr, table);
       if constexpr (TR == 2) {
         const Blk4Tw<GEO, W> gs(t, tf, Rr);
-        fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
+        fwd_rounds<GEO, KIND, TR, B>(lds, x, t, tws, M);
         __builtin_amdgcn_sched_barrier(0);
         W il = 0;
         if constexpr (G::TW_LDS) il = tw_lds_word(ti, t, Rr);
@@ -90,7 +93,7 @@ __device__ __forceinline__ void row_task(const W* A, const W* B, W* Cout, const 
         if constexpr (G::TW_LDS) tw_lds_put<KIND>(table, il, t, M);
         inv_rounds<GEO, KIND, TR, L::B4>(lds, x[0], t, iws, lg - TR, M);
       } else {
-        fwd_rounds<GEO, KIND, TR, L::H>(lds, x, t, tws, M);
+        fwd_rounds<GEO, KIND, TR, B>(lds, x, t, tws, M);
         __builtin_amdgcn_sched_barrier(0);
         W il = 0;
         if constexpr (G::TW_LDS) il = tw_lds_word(ti, t, Rr);

@@ -52,7 +52,7 @@ k_pipe(PipeArgsT<W> a, LimbSetT<W> ls) {
     const size_t off = (size_t)prod * N + ((size_t)row << PIPE_LC);
     const typename ModOf<W>::type M = ls.mod[limb];
     const W* Bp = (MODE == ROW_SQR) ? nullptr : (a.nops == 1 ? a.C : a.WS) + off;
-    row_task<PIPE_LC, KIND, MODE>(a.C + off, Bp, a.C + off, a.twf + (size_t)limb * N, a.twi + (size_t)limb * N,
+    row_task<PIPE_LC, KIND, MODE, col_bound<LOGR, KIND, W>()>(a.C + off, Bp, a.C + off, a.twf + (size_t)limb * N, a.twi + (size_t)limb * N,
                                   R + row, true, false, PIPE_LC + LOGR, M, lds, t);
     return;
   }

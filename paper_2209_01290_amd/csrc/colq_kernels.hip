@@ -79,9 +79,12 @@ __device__ __forceinline__ void colq_fwd(W* buf, W* other, W (&x)[4], const W (&
     ct_lazy<KIND>(x[0], x[1], tw_vec<KIND>(tb[RHO], M), s1.red, s1.k, M);
     ct_lazy<KIND>(x[2], x[3], tw_vec<KIND>(tc[RHO], M), s1.red, s1.k, M);
   }
+  constexpr int OUT = G::len(RHO) == 2 ? s1.out : s0.out;
   if constexpr (RHO + 1 < G::NRND) {
     colq_exchange<G::lq(RHO), G::lq(RHO + 1)>(buf, x, t, j, logcpw);
-    colq_fwd<LOGR, KIND, RHO + 1, (G::len(RHO) == 2 ? s1.out : s0.out)>(other, buf, x, ta, tb, tc, t, j, logcpw, M);
+    colq_fwd<LOGR, KIND, RHO + 1, OUT>(other, buf, x, ta, tb, tc, t, j, logcpw, M);
+  } else {
+    static_assert(OUT == colq_bound<LOGR, KIND, W>() && OUT <= LazyRule<W, KIND>::H, "what the row pass is told");
   }
 }
 

@@ -62,6 +62,17 @@ struct LazyRule<uint64_t, KIND_WIDE> {
   static constexpr int rmax(int v, bool uni) { return 3 * Q1 + ((uni ? 2 : 4) * v + 15) / 16; }
 };
 constexpr int ceil_q(int b) { return (b + Q1 - 1) / Q1; }
+// What the stages rely on: after a reduction a CT butterfly's sum and difference fit H;
+// a GS butterfly on words below GIN fits H, and its product and every word that enters
+// the inverse rounds is below GIN again.
+template <typename W, int KIND>
+constexpr bool rule_holds() {
+  using L = LazyRule<W, KIND>;
+  return 2 * Q1 + ceil_q(L::rmax(L::H, false)) * Q1 <= L::H && 2 * L::GIN <= L::H && L::rmax(L::H, false) <= L::GIN &&
+         L::PW <= L::GIN && L::B4 <= L::GIN;
+}
+static_assert(rule_holds<uint64_t, 0>() && rule_holds<uint64_t, 1>() && rule_holds<uint32_t, 0>() &&
+              rule_holds<uint32_t, 1>(), "KIND_WIDE, KIND_ANY");
 
 // A twiddle and its companion.
 template <typename W>

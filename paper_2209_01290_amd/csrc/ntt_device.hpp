@@ -563,8 +563,12 @@ __device__ __forceinline__ void col_inv(W (&x)[1 << LOGR], const W* __restrict__
   canon_all<KIND>(x, M);
 }
 
-// Bound on the words a forward column pass of 2^LOGR rows leaves (LOGR = 0: none,
-// canonical words), in whichever of the forms here it ran.
+// Bound on the words that a forward column pass of 2^LOGR rows leaves (LOGR = 0:
+// none, canonical words): col_bound for the forms here (col_fwd, col32_fwd_pair),
+// colq_bound for k_colq, whose companions are all tw_vec's. For 64-bit KIND_WIDE
+// and LOGR = 2, 3, 4 the second is the larger: 160, 256, 144 against 144, 224, 112.
+template <int LOGR, int KIND, typename W>
+constexpr int colq_bound() { return ct_bound<W, KIND>(Q1, LOGR, false); }
 template <int LOGR, int KIND, typename W>
 constexpr int col_bound() {
   constexpr int one = ct_bound<W, KIND>(Q1, LOGR, true);

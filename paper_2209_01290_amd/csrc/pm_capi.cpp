@@ -282,9 +282,10 @@ hipError_t run_row(int logc, int kind, int mode, const RowArgsT<W>& a, hipStream
 
 // The column pass of a plan: four words per thread (k_colq) for the
 // small-batch geometry, else one thread per column (k_col).
+bool col_quad(int logr, int ebx) { return ebx == 2 && logr >= (int)PM_COLQ_MIN_LOGR; }
 template <typename W>
 hipError_t run_col(int logr, int kind, bool inv, const ColArgsT<W>& a, hipStream_t s, int ebx) {
-  const bool quad = ebx == 2 && logr >= (int)PM_COLQ_MIN_LOGR;
+  const bool quad = col_quad(logr, ebx);
   ProfScope ps(s, col_name<W>(inv, logr, quad));
   return quad ? launch_colq(logr, kind, inv, a, s) : launch_col(logr, kind, inv, a, s);
 }
@@ -460,7 +461,7 @@ int polymul_common(const W* a, const W* b_, W* c, size_t N, size_t limbs, size_t
     hipError_t e = run_col(p.logr, b.kind, false, cf, s, p.ebx);
     if (e != hipSuccess) return e;
     RowArgsT<W> ra{c + base, square ? nullptr : wb, c + base, tf, ti, b.log2n, p.R, (uint32_t)polys,
-                   (uint32_t)nl, &ls};
+                   (uint32_t)nl, &ls, col_quad(p.logr, p.ebx)};
     if ((e = run_row(p.logc, b.kind, mode, ra, s, ebx, fused)) != hipSuccess) return e;
     ColArgsT<W> ci{c + base, c + base, nullptr, nullptr, ti, b.log2n, (uint32_t)polys, (uint32_t)nl, 1, &ls};
     return run_col(p.logr, b.kind, true, ci, s, p.ebx);

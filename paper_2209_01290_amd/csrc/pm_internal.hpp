@@ -44,6 +44,7 @@ struct RowArgsT {
   const W* twi;           // psi_inv_br, [limbs][N]
   uint32_t log2n, R, polys, limbs;
   const LimbSetT<W>* ls;
+  bool colq = false;      // R > 1: the forward columns were k_colq's (colq_bound)
 };
 using RowArgs = RowArgsT<uint64_t>;
 
@@ -75,7 +76,8 @@ PM_DECL_ROW(8) PM_DECL_ROW(9) PM_DECL_ROW(10) PM_DECL_ROW(11) PM_DECL_ROW(12) PM
 // The product rows (ROW_MUL) of 2^12 words with the split's radix
 // fixed at compile time (row_fixed.inc): 64-bit words with moduli of 34..61
 // bits (row_12r.hip), 32-bit words (row_12r32.hip); false, launching
-// nothing, for other modes, kinds or shapes.
+// nothing, for other modes, kinds or shapes, or for words of k_colq that may be
+// beyond its bound.
 bool launch_row12_fixed(int kind, int mode, const RowArgs& a, hipStream_t s);
 bool launch_row12_fixed(int kind, int mode, const RowArgsT<uint32_t>& a, hipStream_t s);
 hipError_t launch_col(int logr, int kind, bool inv, const ColArgs& a, hipStream_t s);

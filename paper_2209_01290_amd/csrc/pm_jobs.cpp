@@ -246,7 +246,7 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
         ok = add(G_COLF, PH_COLF, (uint64_t)J.nops * J.count * cbs) && add(G_COLI, PH_COLI, (uint64_t)J.count * cbs);
       }
       const int g = J.logc <= 11 ? G_ROW11 : (J.logc == 12 ? G_ROW12 : (J.logc == 13 ? G_ROW13 : G_ROW14));
-      const uint64_t rows_per_item = J.logc <= 12 ? (4096u >> J.logc) : 1;   // RowGeom<logc>::ROWS
+      const uint64_t rows_per_item = jobs_rows_per_item(J.logc);
       const uint64_t tasks = (uint64_t)J.count * R;
       ok = ok && add(g, PH_ROW, (tasks + rows_per_item - 1) / rows_per_item);
     }

@@ -23,6 +23,10 @@ struct JobDev {
   uint32_t first[4];       // first work item of the job in each phase's numbering
 };
 
+// Rows of 2^logc words in one work item of the row phase: a workgroup's (job_row asserts
+// it). Rows of up to 16 words are one thread's, so 256 of them whatever their length.
+constexpr uint32_t jobs_rows_per_item(uint32_t logc) { return logc < 4 ? 256u : (logc < 12 ? 4096u >> logc : 1u); }
+
 // One launch of the software-pipelined job table (k_jobs_pipe): nr row work
 // items from r0 of the row map, then nf forward-column items from f0 and ni
 // inverse-column items from i0 of the column maps.

@@ -82,3 +82,36 @@ def test_job_rows(rows, mix):
         L.pm_tune_set_jobs_pipeline(-1)
         for n, c in before.items():
             L.pm_tune_set(L.OP_POLYMUL, n, c)
+
+
+# rows of up to 16 words are one thread's: 256 products to a work item, whatever N
+@pytest.mark.parametrize("count", [255, 256, 257, 700])
+@pytest.mark.parametrize("log2n", [1, 2, 3, 4, 5])
+def test_job_short_rows(log2n, count):
+    import torch
+    from paper_2209_01290_amd import lib as L
+    N, q = 1 << log2n, L.pm_ntt_primes(1 << log2n, 1, 60)[0]
+    a, b = synth.operands(synth.SEED_BASE + 7, [q], count, N)
+    fw, iv = oracle_tables([q], N)
+    want = oracle_polymul(a, b, [q], N, fw, iv)
+    dfw, div = (L.to_device(x) for x in L.pm_make_tables(q, N))
+    da, db = L.to_device(a[0]), L.to_device(b[0])
+    c = torch.full((count * N + 64,), -1, dtype=torch.int64, device="cuda")
+    jobs = [L.make_job(log2n, count, q, dfw, div, da, db, c)]
+    ws = torch.empty((L.pm_polymul_jobs_workspace_bytes(jobs) + 7) // 8, dtype=torch.int64, device="cuda")
+
+    def check(what):
+        got = L.to_host(c)
+        assert (got[count * N:] == np.uint64(2**64 - 1)).all()
+        msg = first_mismatch(got[: count * N], want)
+        assert msg is None, "%s N 2^%d x %d: %s" % (what, log2n, count, msg)
+
+    L.pm_polymul_jobs(jobs, ws)
+    check("jobs")
+    c.fill_(-1)
+    plan = L.pm_plan_create(jobs)
+    try:
+        L.pm_plan_launch(plan)
+        check("plan")
+    finally:
+        L.pm_plan_destroy(plan)

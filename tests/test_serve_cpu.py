@@ -185,3 +185,41 @@ def test_out_of_order_completion_is_recorded_at_once():
     assert reqs[1].t_done - reqs[1].arrival < 0.02      # not held behind the 50 ms batch
     assert reqs[2].t_done - reqs[2].arrival < 0.02
     assert eng.arena.used == 0
+
+
+def _job_bytes(requests):
+    """What the library asks for a batch of these requests, (log2n, limbs) each, in one job call."""
+    from paper_2209_01290_amd import lib
+    rows = np.zeros(sum(L for _, L in requests), dtype=serve.JOB_DTYPE)
+    i = 0
+    for log2n, limbs in requests:
+        r = rows[i:i + limbs]
+        r["log2n"], r["count"] = log2n, 1
+        r["q"] = lib.pm_ntt_primes(1 << log2n, 1, 60)[0]
+        # addresses that are never read: distinct tables, a != b
+        base = np.uint64(1 << 20) + np.arange(i, i + limbs, dtype=np.uint64) * np.uint64(1 << 12)
+        for k, f in enumerate(("psi_br", "psi_inv_br", "a", "b", "c")):
+            r[f] = base + np.uint64(256 * k)
+        i += limbs
+    return lib.pm_polymul_jobs_workspace_bytes_raw(rows.ctypes.data, len(rows))
+
+
+@pytest.mark.parametrize("chunks", [-1, 0, 2, 256])
+@pytest.mark.parametrize("db", [False, True])
+def test_charge_covers_the_job_call(db, chunks):
+    """The workspace of a batch's block is at least what pm_polymul_jobs asks for: every
+    size alone, from one product to batches that run pipelined, and mixed traces."""
+    from gpu_helpers import tuned
+    from paper_2209_01290_amd import lib
+    lib.load()
+    with tuned(lib):
+        if not db:
+            for n in range(1, 18):
+                lib.pm_tune_set(lib.OP_POLYMUL, n, 0)
+        lib.pm_tune_set_jobs_pipeline(chunks)
+        batches = [[(n, L)] * k for n in range(13, 18) for L in (1, 30, 60) for k in (1, 4, 12, 68)]
+        batches += [[(n, L) for _, n, L in _trace(k, 1000.0, seed=k)] for k in (2, 9, 130)]
+        for batch in batches:
+            charge = sum(serve.request_bytes(n, L) - serve.footprint(n, L) for n, L in batch)
+            need = _job_bytes(batch)
+            assert 0 < need <= charge + serve.BATCH_WS_SLACK, (batch[0], len(batch), need - charge)

@@ -111,12 +111,11 @@ def footprint(log2n: int, limbs: int) -> int:
 
 def request_workspace(log2n: int, limbs: int) -> int:
     """Upper bound of the workspace bytes a request adds to its batch: the
-    column-pass copy of b when the product runs in two passes, plus its
-    job-table entries (one record of at most 256 bytes and at most 128
+    column-pass copy of b (a product of any size may run in two passes: a
+    request alone in its batch takes the small-batch plan), plus its job-table entries (one record of at most 256 bytes and at most 128
     work-item slots of 4 bytes per limb: N = 2^17 in the pipelined form has 32
     row, 64 forward and 32 inverse column items a product)."""
-    N = 1 << log2n
-    return (N * limbs * 8 if log2n > 12 else 0) + limbs * 768
+    return (8 << log2n) * limbs + limbs * 768
 
 
 def request_bytes(log2n: int, limbs: int) -> int:

@@ -223,3 +223,23 @@ def test_charge_covers_the_job_call(db, chunks):
             charge = sum(serve.request_bytes(n, L) - serve.footprint(n, L) for n, L in batch)
             need = _job_bytes(batch)
             assert 0 < need <= charge + serve.BATCH_WS_SLACK, (batch[0], len(batch), need - charge)
+
+
+@pytest.mark.parametrize("db", [False, True])
+def test_charge_covers_the_single_request_call(db):
+    """A batch of one request runs as pm_polymul, which takes no workspace size: the
+    charge must hold what it writes there, under every plan a request of any size meets."""
+    from gpu_helpers import tuned
+    from paper_2209_01290_amd import lib
+    lib.load()
+    with tuned(lib):
+        for log2n in range(1, 18):
+            plans = [None] if db else [(c, 4) for c in range(5, min(log2n, 12) + 1)
+                                       if log2n - c <= 7 and not (log2n - c == 1 and c < 8)] or [None]
+            for plan in plans:
+                if plan:
+                    lib.pm_tune_set_small(lib.OP_POLYMUL, log2n, *plan)
+                    lib.pm_tune_set_small_limit(lib.OP_POLYMUL, log2n, 1 << 40)
+                for limbs in (1, 2, 31, 60):
+                    need = lib.pm_polymul_workspace_bytes(1 << log2n, limbs, 1)
+                    assert need <= serve.request_workspace(log2n, limbs), (log2n, limbs, plan)

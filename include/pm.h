@@ -115,8 +115,10 @@ int pm_polymul_fused(const uint64_t *a, const uint64_t *b, uint64_t *c, size_t N
                      const uint64_t *psi_inv_br, void *workspace, pm_stream_t stream);
 
 /* Workspace bytes pm_polymul and pm_polymul_fused need for this shape (0 if
- * none). It follows the plan of this very shape: a larger batch of the same N
- * may be one pass and need less, so query every shape that is multiplied. */
+ * none). With the built-in plans and with the packaged tuning table it never falls as the
+ * batch grows, so one query for the largest batch of an N serves the smaller
+ * ones. Plans set by hand (pm_tune_set_small) can make a large batch one pass above small
+ * batches of two: query every shape then, or see pm_tune_hold_workspace. */
 size_t pm_polymul_workspace_bytes(size_t N, size_t limbs, size_t polys_per_limb);
 
 /*
@@ -128,8 +130,8 @@ size_t pm_polymul_workspace_bytes(size_t N, size_t limbs, size_t polys_per_limb)
  * PM_NOALLOC_SCRATCH_BYTES (64 MiB) per GPU, created when the library is
  * loaded on that GPU and held until the process ends; its address is looked
  * up on the first call for each device (the stream's device).
- * Limit: batches with pm_polymul_workspace_bytes(N, limbs, polys_per_limb)
- * above PM_NOALLOC_SCRATCH_BYTES return PM_EINVAL before any work is queued
+ * Limit: batches whose own plan needs more workspace than
+ * PM_NOALLOC_SCRATCH_BYTES return PM_EINVAL before any work is queued
  * (e.g. at most 128 products of N = 2^16, or 64 of N = 2^17, per call; batches
  * needing no workspace have no limit).
  * Every call on one GPU shares that GPU's array: calls that may overlap on one
@@ -292,12 +294,15 @@ int pm_tune_get(int op, unsigned log2n);   /* current logc, or PM_EINVAL */
  * with N); max_words = 0 restores the global threshold;
  * pm_tune_get_small_limit returns 0 when none is set (or for an invalid
  * op / N). Results are identical under every plan; workspace sizes follow
- * the plan in use.
+ * the plan in use. pm_tune_hold_workspace(log2n, 1) makes the product's workspace
+ * queries for N = 2^log2n hold for every smaller batch too (0: the batch's own plan
+ * alone; pm_tune_set_small for the product restores that).
  */
 int pm_tune_set_small(int op, unsigned log2n, unsigned logc, unsigned words_per_thread);
 int pm_tune_get_small(int op, unsigned log2n, unsigned *logc, unsigned *words_per_thread);
 int pm_tune_set_small_batch(size_t max_words);
 size_t pm_tune_get_small_batch(void);
+int pm_tune_hold_workspace(unsigned log2n, int on);
 int pm_tune_set_small_limit(int op, unsigned log2n, size_t max_words);
 size_t pm_tune_get_small_limit(int op, unsigned log2n);
 

@@ -366,8 +366,7 @@ int ntt_common(W* x, size_t N, size_t limbs, size_t polys, const W* q, const W* 
 template <typename W>
 size_t polymul_workspace(size_t N, size_t limbs, size_t polys) {
   if (!is_pow2(N) || N < 2 || N > ((size_t)1 << PM_MAX_LOG2N)) return 0;
-  const PassPlan p = plan_for(OP_POLYMUL, log2u(N), N * limbs * polys);
-  return p.R > 1 ? N * limbs * polys * sizeof(W) : 0;
+  return plan_workspace_words(log2u(N), N * limbs * polys) * sizeof(W);
 }
 
 // Chunks of the software-pipelined product for a launch group of np
@@ -479,7 +478,9 @@ namespace pm {
 int polymul_fixed_workspace(const uint64_t* a, const uint64_t* b, uint64_t* c, size_t N, size_t limbs,
                             size_t polys, const uint64_t* q, const uint64_t* psi_br, const uint64_t* psi_inv_br,
                             void* workspace, size_t workspace_cap, pm_stream_t stream) {
-  const size_t need = polymul_workspace<uint64_t>(N, limbs, polys);
+  const size_t words = N * limbs * polys;      // of this very batch
+  const bool sized = is_pow2(N) && N >= 2 && N <= ((size_t)1 << PM_MAX_LOG2N);
+  const size_t need = sized && plan_for(OP_POLYMUL, log2u(N), words).R > 1 ? words * sizeof(uint64_t) : 0;
   if (need > workspace_cap)
     return fail(PM_EINVAL, "pm_polymul_noalloc: this batch needs " + std::to_string(need) +
                                " bytes of workspace, above the library's fixed " + std::to_string(workspace_cap) +

@@ -1,6 +1,7 @@
 // Pass-plan table (see pm_plan.hpp).
 #include "pm_plan.hpp"
 
+#include <algorithm>
 #include <atomic>
 
 #include "../../include/pm.h"
@@ -16,6 +17,8 @@ std::atomic<uint32_t> g_small[OP_COUNT][PM_MAX_LOG2N + 1];
 std::atomic<size_t> g_small_words{0};
 // per (op, log2n) batch limit of the small-batch plan; 0 = g_small_words
 std::atomic<size_t> g_small_limit[OP_COUNT][PM_MAX_LOG2N + 1];
+// per log2n: workspace queries hold for smaller batches (plan_workspace_words)
+std::atomic<bool> g_hold[PM_MAX_LOG2N + 1];
 std::atomic<int> g_pipe{-1};
 
 bool valid_split(unsigned log2n, unsigned logc) {
@@ -55,11 +58,13 @@ bool plan_set(int op, unsigned log2n, unsigned logc) {
 
 bool plan_small_set(int op, unsigned log2n, unsigned logc, unsigned ebx) {
   if (op < 0 || op >= OP_COUNT || log2n < 1 || log2n > PM_MAX_LOG2N) return false;
-  if (logc == 0) { g_small[op][log2n].store(0); return true; }
-  if (ebx != 2 && ebx != 4) return false;
-  if (ebx == 4 && !valid_split(log2n, logc)) return false;
-  if (ebx == 2 && !valid_small_split(log2n, logc)) return false;
-  g_small[op][log2n].store(logc | (ebx << 8));
+  if (logc != 0) {
+    if (ebx != 2 && ebx != 4) return false;
+    if (ebx == 4 && !valid_split(log2n, logc)) return false;
+    if (ebx == 2 && !valid_small_split(log2n, logc)) return false;
+  }
+  if (op == OP_POLYMUL) g_hold[log2n].store(false);
+  g_small[op][log2n].store(logc ? logc | (ebx << 8) : 0);
   return true;
 }
 
@@ -135,6 +140,21 @@ PassPlan plan_for(int op, unsigned log2n, size_t batch_words) {
   return plan_for(op, log2n);
 }
 
+bool plan_hold_set(unsigned log2n, bool on) {
+  if (log2n < 1 || log2n > PM_MAX_LOG2N) return false;
+  g_hold[log2n].store(on);
+  return true;
+}
+
+size_t plan_workspace_words(unsigned log2n, size_t batch_words) {
+  if (plan_for(OP_POLYMUL, log2n, batch_words).R > 1) return batch_words;
+  if (!g_hold[log2n].load()) return 0;
+  const uint32_t v = g_small[OP_POLYMUL][log2n].load();
+  if (!v || (v & 0xff) == log2n) return 0;
+  const size_t limit = plan_small_limit(OP_POLYMUL, log2n);
+  return std::min(batch_words, limit ? limit : g_small_words.load());
+}
+
 }  // namespace pm
 
 extern "C" int pm_tune_set(int op, unsigned log2n, unsigned logc) {
@@ -172,6 +192,10 @@ extern "C" int pm_tune_set_small_limit(int op, unsigned log2n, size_t max_words)
 }
 
 extern "C" size_t pm_tune_get_small_limit(int op, unsigned log2n) { return pm::plan_small_limit(op, log2n); }
+
+extern "C" int pm_tune_hold_workspace(unsigned log2n, int on) {
+  return pm::plan_hold_set(log2n, on != 0) ? PM_OK : PM_EINVAL;
+}
 
 extern "C" int pm_tune_set_pipeline(int chunks) {
   pm::plan_pipe_set(chunks);

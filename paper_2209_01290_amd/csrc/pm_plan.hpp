@@ -43,6 +43,11 @@ size_t plan_small_threshold();
 // threshold above); false for an invalid (op, log2n).
 bool plan_small_limit_set(int op, unsigned log2n, size_t words);
 size_t plan_small_limit(int op, unsigned log2n);
+// Words of b's copy that a product workspace query answers for: the batch's own
+// under its plan, and with hold set those of every smaller batch too (a small-batch
+// plan in two passes below a single pass). plan_small_set clears hold.
+bool plan_hold_set(unsigned log2n, bool on);
+size_t plan_workspace_words(unsigned log2n, size_t batch_words);
 // Limb chunks of the software-pipelined product: -1 = the built-in choice,
 // 0 or 1 = never pipelined, G >= 2 = G chunks (at most the launch group's limbs).
 void plan_pipe_set(int chunks);

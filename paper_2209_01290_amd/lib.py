@@ -95,6 +95,7 @@ def load():
                                         ctypes.POINTER(ctypes.c_uint)]),
             "pm_tune_set_small_batch": (i32, [sz]),
             "pm_tune_get_small_batch": (sz, []),
+            "pm_tune_hold_workspace": (i32, [ctypes.c_uint, i32]),
             "pm_tune_set_small_limit": (i32, [i32, ctypes.c_uint, sz]),
             "pm_tune_get_small_limit": (sz, [i32, ctypes.c_uint]),
             "pm_tune_set_pipeline": (i32, [i32]),
@@ -152,7 +153,7 @@ def exported_symbols():
             "pm_tune_set_small_batch", "pm_tune_get_small_batch", "pm_tune_set_small_limit",
             "pm_tune_get_small_limit", "pm_tune_set_pipeline", "pm_tune_get_pipeline",
             "pm_tune_set_pipeline_rows", "pm_tune_get_pipeline_rows", "pm_tune_set_jobs_pipeline",
-            "pm_tune_get_jobs_pipeline"]
+            "pm_tune_get_jobs_pipeline", "pm_tune_hold_workspace"]
 
 
 def _check(rc: int, func: str):
@@ -460,6 +461,11 @@ def pm_tune_get_small_batch():
     return int(load().pm_tune_get_small_batch())
 
 
+def pm_tune_hold_workspace(log2n, on=True):
+    """The product's workspace queries for N = 2^log2n hold for smaller batches too."""
+    _check(load().pm_tune_hold_workspace(log2n, int(on)), "pm_tune_hold_workspace")
+
+
 def pm_tune_set_small_limit(op, log2n, max_words):
     """Batch limit (words) of the small-batch plan of (op, N); 0 = the global threshold."""
     _check(load().pm_tune_set_small_limit(op, log2n, max_words), "pm_tune_set_small_limit")
@@ -524,6 +530,8 @@ def apply_tune_db(path=None):
         for name, table in small.get("choices", {}).items():
             for log2n, (logc, wpt) in table.items():
                 pm_tune_set_small(ops[name], int(log2n), int(logc), int(wpt))
+                if name == "polymul":       # a workspace sized for the largest batch serves every batch
+                    pm_tune_hold_workspace(int(log2n))
                 n += 1
         for name, table in small.get("limits", {}).items():
             for log2n, words in table.items():

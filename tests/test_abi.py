@@ -289,3 +289,27 @@ def test_pipeline_rows_setting():
     finally:
         for r, v in before.items():
             L.pm_tune_set_pipeline_rows(r, v)
+
+
+def test_workspace_of_the_largest_batch_serves_smaller_ones():
+    """With the packaged table the product's workspace never falls as the batch grows
+    (pm_polymul takes no size), on both word types; a product that is one pass needs none."""
+    from gpu_helpers import tuned
+    from paper_2209_01290_amd import lib as L
+    L.load()
+    shapes = sorted({(l, p) for l in (1, 3, 5, 48) for p in [1, 2, 3] + [1 << k for k in range(2, 13)]},
+                    key=lambda s: s[0] * s[1])
+    with tuned(L):
+        for log2n in range(1, 18):
+            for query, size in ((L.pm_polymul_workspace_bytes, 8), (L.pm_polymul_u32_workspace_bytes, 4)):
+                largest = 0
+                for limbs, polys in shapes:
+                    need = query(1 << log2n, limbs, polys)
+                    assert need >= largest, (log2n, limbs, polys)
+                    assert need <= (size * limbs * polys) << log2n
+                    largest = need
+        for bad in (0, 18):
+            with pytest.raises(L.PMError):
+                L.pm_tune_hold_workspace(bad)
+    # without a held table the query is the batch's own
+    assert L.pm_polymul_workspace_bytes(1 << 13, 1, 4) == 0

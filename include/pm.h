@@ -222,9 +222,11 @@ typedef struct {
  * One-shot form: validates the jobs, uploads a job table into `workspace`
  * (device, 256-byte aligned, at least pm_polymul_jobs_workspace_bytes()
  * bytes; it also holds intermediates) and enqueues the passes on `stream`.
- * The host job array may be reused as soon as the call returns.
+ * The host job array may be reused as soon as the call returns. The query is enough
+ * for every part of the batch too (jobs left out, lower counts); 0 if the batch is
+ * invalid.
  */
-size_t pm_polymul_jobs_workspace_bytes(const pm_job *jobs, size_t njobs); /* 0 if invalid */
+size_t pm_polymul_jobs_workspace_bytes(const pm_job *jobs, size_t njobs);
 int pm_polymul_jobs(const pm_job *jobs, size_t njobs, void *workspace, size_t workspace_bytes,
                     pm_stream_t stream);
 

@@ -149,6 +149,44 @@ std::vector<uint32_t> table_order(const std::vector<JobDev>& jobs) {
   return order;
 }
 
+// Rows of a job are 2^logc words: of N >= 2^12, 2^12 in the pipelined form and in the
+// three-pass form without the tuned splits.
+uint32_t job_logc(const JobDev& J, bool pipelined, bool tuned) {
+  return J.log2n >= 12 && (pipelined || !tuned) ? 12 : plan_for(OP_POLYMUL, J.log2n).logc;
+}
+
+// A job's work items: their number by map and phase (add, false where it refuses).
+template <class F>
+bool job_items(const JobDev& J, uint32_t logc, bool pipelined, F add) {
+  const uint32_t logr = J.log2n - logc;
+  const uint64_t R = 1ull << logr;
+  if (pipelined && J.log2n >= 12) {
+    const uint64_t cols = R > 1 ? (uint64_t)pipe_col_blocks(logr) * J.count : 0;
+    return add(G_PROW, PH_ROW, J.count * R) && add(G_PCOLF, PH_COLF, cols * J.nops) && add(G_PCOLI, PH_COLI, cols);
+  }
+  if (R > 1) {
+    const uint64_t cols = (uint64_t)J.count << (logc - 8);
+    if (!add(G_COLF, PH_COLF, J.nops * cols) || !add(G_COLI, PH_COLI, cols)) return false;
+  }
+  const int g = logc <= 11 ? G_ROW11 : (logc == 12 ? G_ROW12 : (logc == 13 ? G_ROW13 : G_ROW14));
+  const uint64_t rows_per_item = jobs_rows_per_item(logc);
+  return add(g, PH_ROW, (J.count * R + rows_per_item - 1) / rows_per_item);
+}
+
+// Bytes of the blob in one form of the layout.
+size_t form_bytes(const std::vector<JobDev>& jobs, bool pipelined, bool tuned) {
+  uint64_t items[NGROUP] = {};
+  size_t ws = 0;
+  for (const JobDev& J : jobs) {
+    const uint32_t logc = job_logc(J, pipelined, tuned);
+    job_items(J, logc, pipelined, [&](int g, int, uint64_t n) { items[g] += n; return true; });
+    if (logc < J.log2n && J.nops == 2) ws += ((size_t)J.count << J.log2n) * sizeof(uint64_t);
+  }
+  size_t off = align_up(jobs.size() * sizeof(JobDev), 256);
+  for (const uint64_t n : items) off = align_up(off + n * sizeof(uint32_t), 256);
+  return off + ws;
+}
+
 int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
   if (!jobs || njobs == 0) return set_error(PM_EINVAL, "empty job list");
   if (njobs > (1u << 24)) return set_error(PM_EINVAL, "too many jobs");
@@ -208,16 +246,9 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
   std::vector<uint32_t> pjobs;
   for (const uint32_t j : order) {
     JobDev& J = L->jobs[j];
-    const bool pj = pipelined && J.log2n >= 12;
-    if (pj) {
-      J.logc = 12;
-      J.logr = J.log2n - 12;
-      pjobs.push_back((uint32_t)j);
-    } else {
-      const PassPlan p = plan_for(OP_POLYMUL, J.log2n);
-      J.logc = (J.log2n >= 12 && !tuned_rows) ? 12 : p.logc;
-      J.logr = J.log2n - J.logc;
-    }
+    if (pipelined && J.log2n >= 12) pjobs.push_back((uint32_t)j);
+    J.logc = job_logc(J, pipelined, tuned_rows);
+    J.logr = J.log2n - J.logc;
     if (J.logr > 0 && J.nops == 2) {
       ws_job[j] = ws;
       ws += ((size_t)J.count << J.log2n) * sizeof(uint64_t);
@@ -227,29 +258,13 @@ int build_layout(const pm_job* jobs, size_t njobs, Layout* L) {
   // item is recorded (also when the job has none in that phase)
   for (const uint32_t j : order) {
     JobDev& J = L->jobs[j];
-    const uint32_t R = 1u << J.logr;
-    const bool pj = pipelined && J.log2n >= 12;
     auto add = [&](int g, int phase, uint64_t n) -> bool {
       if (L->map[g].size() + n > 0x7fffffffull) return false;
       J.first[phase] = (uint32_t)L->map[g].size();
       L->map[g].insert(L->map[g].end(), n, (uint32_t)j);
       return true;
     };
-    bool ok = true;
-    if (pj) {
-      const uint64_t cols = R > 1 ? (uint64_t)pipe_col_blocks(J.logr) * J.count : 0;
-      ok = add(G_PROW, PH_ROW, (uint64_t)J.count * R) && add(G_PCOLF, PH_COLF, cols * J.nops) &&
-           add(G_PCOLI, PH_COLI, cols);
-    } else {
-      if (R > 1) {
-        const uint64_t cbs = 1ull << (J.logc - 8);
-        ok = add(G_COLF, PH_COLF, (uint64_t)J.nops * J.count * cbs) && add(G_COLI, PH_COLI, (uint64_t)J.count * cbs);
-      }
-      const int g = J.logc <= 11 ? G_ROW11 : (J.logc == 12 ? G_ROW12 : (J.logc == 13 ? G_ROW13 : G_ROW14));
-      const uint64_t rows_per_item = jobs_rows_per_item(J.logc);
-      const uint64_t tasks = (uint64_t)J.count * R;
-      ok = ok && add(g, PH_ROW, (tasks + rows_per_item - 1) / rows_per_item);
-    }
+    const bool ok = job_items(J, J.logc, pipelined, add);
     if (!ok) return set_error(PM_EINVAL, "batch has more than 2^31 work items in one pass");
   }
   if (pipelined) {
@@ -378,7 +393,10 @@ extern "C" {
 size_t pm_polymul_jobs_workspace_bytes(const pm_job* jobs, size_t njobs) {
   Layout L;
   if (build_layout(jobs, njobs, &L) != PM_OK) return 0;
-  return L.ws_off + L.ws_bytes;
+  // Part of these jobs may take another three-pass form than all of them do (fewer long
+  // rows: rows of 2^12 words, fewer sizes: the tuned ones), each of which grows with the
+  // batch; the pipelined form is never a part's alone.
+  return std::max({L.ws_off + L.ws_bytes, form_bytes(L.jobs, false, false), form_bytes(L.jobs, false, true)});
 }
 
 int pm_polymul_jobs(const pm_job* jobs, size_t njobs, void* workspace, size_t workspace_bytes, pm_stream_t stream) {

@@ -313,3 +313,37 @@ def test_workspace_of_the_largest_batch_serves_smaller_ones():
                 L.pm_tune_hold_workspace(bad)
     # without a held table the query is the batch's own
     assert L.pm_polymul_workspace_bytes(1 << 13, 1, 4) == 0
+
+
+@pytest.mark.parametrize("chunks", [-1, 0, 4])
+def test_jobs_workspace_serves_parts_of_the_batch(chunks):
+    """pm_polymul_jobs_workspace_bytes of a batch is enough for every part of it,
+    whichever rows and form the part takes (tuned rows of 2^11, 2^13 and 2^14 words, rows of
+    2^12, pipelined). No pointer is read."""
+    import random
+    from gpu_helpers import tuned
+    from paper_2209_01290_amd import lib as L
+    L.load()
+    q = {n: L.pm_ntt_primes(1 << n, 1, 60)[0] for n in range(1, 18)}
+
+    def need(batch):
+        jobs = [L.Job(n, count, q[n], *(p + 4096 * (i + 1) for p in (8, 16, 24, 24 if square else 32, 40)))
+                for i, (n, count, square) in enumerate(batch)]
+        return L.pm_polymul_jobs_workspace_bytes(jobs)
+
+    rnd = random.Random(17)
+    with tuned(L):
+        for rows in ({}, {13: 13, 14: 13, 15: 13}, {14: 14}, {12: 11, 13: 11}, {12: 12, 13: 10}):
+            for n, c in rows.items():
+                L.pm_tune_set(L.OP_POLYMUL, n, c)
+            L.pm_tune_set_jobs_pipeline(chunks)
+            batches = [[(13, 600, False)], [(14, 300, False)], [(13, 511, False), (12, 3, False)],
+                       [(13, 512, False), (16, 1, False)]]
+            batches += [[(rnd.randint(*span), rnd.choice((1, 2, 60, 300)), rnd.random() < 0.2) for _ in range(rnd.randint(2, 9))]
+                        for span in ((1, 17), (12, 14), (13, 13), (12, 17)) for _ in range(6)]
+            for batch in batches:
+                whole = need(batch)
+                for _ in range(8):
+                    part = [(n, rnd.choice((c, max(1, c // 2), 1)), s) for n, c, s in
+                            rnd.sample(batch, rnd.randint(1, len(batch)))]
+                    assert 0 < need(part) <= whole, (batch, part)

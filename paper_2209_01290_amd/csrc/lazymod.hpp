@@ -26,8 +26,9 @@
 // weighted by issue rate: 14 instructions for a CT butterfly and 15 for a GS one
 // plus about 1.3 to 2 for reductions, against 32 and 40.8 with Alg. 4 and full
 // reductions in every butterfly. The product rows of N = 2^16 x 384 (6144 rows
-// of 2^12 words) went from 0.447 to 0.30 ms, 11,116 to 6,300 VALU instructions
-// a thread. Under them the clock falls to 2.15 of 2.4 GHz (the power limit).
+// of 2^12 words) went from 0.447 to 0.27 ms, 11,116 to 5,700 VALU instructions
+// a thread (the products modulo x^4 - g below among them). Under them the clock
+// falls to 2.15 of 2.4 GHz (the power limit).
 //
 // Two rules per word type (LazyRule<W, KIND>); bounds are in sixteenths of q:
 //   64-bit, KIND_WIDE (34 <= len(q) <= 60): H = 16; words may grow over several

@@ -35,7 +35,9 @@
 //
 // Two instantiations:
 //   KIND_WIDE  every modulus of the launch has 34 <= m <= 61 (all 60-bit NTT
-//              primes); the cross sums of c*mu' then fit 64 bits.
+//              primes); the cross sums of c*mu' then fit 64 bits. (mod_kind: the
+//              elementwise product and the per-stage path. The transforms' KIND_WIDE
+//              ends at 60 bits: lazy_kind.)
 //   KIND_ANY   any 2 <= m <= 62: window and final shift chosen per modulus,
 //              carries of c*mu' kept explicitly.
 #pragma once
@@ -44,7 +46,7 @@
 
 namespace pm {
 
-// Per-modulus constants, computed on the host (pm_params.cpp).
+// Per-modulus constants, computed on the host (make_mod).
 struct Mod {
   uint64_t q;      // odd modulus, len(q) = m <= 62
   uint64_t mu;     // mu' as described above

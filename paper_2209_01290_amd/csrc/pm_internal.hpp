@@ -74,7 +74,7 @@ PM_DECL_ROW(1) PM_DECL_ROW(2) PM_DECL_ROW(3) PM_DECL_ROW(4) PM_DECL_ROW(5) PM_DE
 PM_DECL_ROW(8) PM_DECL_ROW(9) PM_DECL_ROW(10) PM_DECL_ROW(11) PM_DECL_ROW(12) PM_DECL_ROW(13) PM_DECL_ROW(14)
 #undef PM_DECL_ROW
 // The product rows (ROW_MUL) of 2^12 words with the split's radix
-// fixed at compile time (row_fixed.inc): 64-bit words with moduli of 34..61
+// fixed at compile time (row_fixed.inc): 64-bit words with moduli of 34..60
 // bits (row_12r.hip), 32-bit words (row_12r32.hip); false, launching
 // nothing, for other modes, kinds or shapes, or for words of k_colq that may be
 // beyond its bound.

@@ -1,5 +1,5 @@
 // Product rows of 2^12 words with the split's radix fixed at compile time,
-// 64-bit words, moduli of 34..61 bits (KIND_WIDE: every 60-bit NTT prime).
+// 64-bit words, moduli of 34..60 bits (the transforms' KIND_WIDE).
 #include "row_fixed.inc"
 
 namespace pm {

@@ -644,12 +644,14 @@ static int il_plan(unsigned n, int maxlast, int* sizes) {
 // Passes of N = 2^n with an LDS row: sizes[0..n-2] register blocks, sizes[n-1]
 // the row. One pass up to 2^10; beyond, the row that measured best (N = 2^11..2^17,
 // batches of 2^22 and 2^25 words): radix-2^4 and 2^5 blocks and rows of 2^8 (four
-// workgroups to a CU) run nearest to the memory's rate, so a pass more, 4 + 4 + 8, beats
-// 6 + 10 for the transforms of 2^16 (275 us against 292 at 2^25 words), not for its
-// products, which would move three batches more (882 against 795).
-static int il_row_plan(unsigned n, bool mul, int* sizes) {
-  static const uint8_t rows[2][7] = {{7, 8, 8, 8, 9, 8, 8}, {7, 8, 8, 9, 9, 10, 8}};    // N = 2^11..2^17
-  const unsigned row = n <= (unsigned)IL_ROW_MAX ? n : rows[mul][n - IL_ROW_MAX - 1];
+// workgroups to a CU) run nearest to the memory's rate. For transforms of 2^16 they are a
+// pass more, 4 + 4 + 8, than rows of 2^10, which pays while the GPU is not full: 2^20, 2^22
+// words 31, 43 us against 40, 45 as 6 + 10; 2^24, 2^28 words 165, 2773 against 144, 2092.
+// (The products' other pass would move three batches more: 6 + 10 + 6 always.)
+static int il_row_plan(unsigned n, bool mul, size_t words, int* sizes) {
+  static const uint8_t rows[2][7] = {{7, 8, 8, 8, 9, 10, 8}, {7, 8, 8, 9, 9, 10, 8}};    // N = 2^11..2^17
+  unsigned row = n <= (unsigned)IL_ROW_MAX ? n : rows[mul][n - IL_ROW_MAX - 1];
+  if (n == 16 && !mul && words <= ((size_t)1 << 22)) row = 8;
   const int np = n > row ? il_plan(n - row, IL_MAXR, sizes) : 0;
   sizes[np] = (int)row;
   return np + 1;
@@ -688,9 +690,14 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   if ((rc = check_ptr(x, "x")) || (rc = check_ptr(tw, inv ? "psi_inv_br" : "psi_br"))) return rc;
   int sz[32];
   // the last pass (the first one back) is an LDS row, which scales by 1/N; one register
-  // block does up to 2^6 (N = 2^6 x 65535: 22.0 us, as rows 26.0)
-  const bool row = b.log2n > (unsigned)IL_MAXR;
-  const int np = row ? il_row_plan(b.log2n, false, sz) : il_plan(b.log2n, IL_MAXR, sz);
+  // block does up to 2^6 (N = 2^6 x 65535: 22.0 us, as rows 26.0). N = 2^17 is three passes
+  // either way, and a row pass touches single lines where a block touches runs of four: from
+  // the size where the batch is far beyond the last-level cache, blocks alone (6 + 6 + 5) are
+  // the faster form (2^24, 2^26, 2^27, 2^28 words: 160, 692, 1271, 2504 us against 153, 682,
+  // 1301, 2783).
+  const size_t words = N * limbs * polys;
+  const bool row = b.log2n > (unsigned)IL_MAXR && !(b.log2n == PM_MAX_LOG2N && words >= IL_BLOCK_WORDS);
+  const int np = row ? il_row_plan(b.log2n, false, words, sz) : il_plan(b.log2n, IL_MAXR, sz);
   hipStream_t s = (hipStream_t)stream;
   if (validate_enabled() &&
       (rc = validate_batch<uint64_t>(b, {{x, "x"}}, {{tw, inv ? "psi_inv_br" : "psi_br"}}, s)))
@@ -751,7 +758,7 @@ int pm_polymul_il(const uint64_t* a, const uint64_t* b_, uint64_t* c, size_t N, 
   int sz[32];
   const bool needs_ws = il_plan(b.log2n, IL_MUL_MAXR, sz) > 1;
   const bool row = b.log2n >= (unsigned)IL_ROW_MIN;
-  const int np = row ? il_row_plan(b.log2n, true, sz) : il_plan(b.log2n, IL_MUL_MAXR, sz);
+  const int np = row ? il_row_plan(b.log2n, true, N * limbs * polys, sz) : il_plan(b.log2n, IL_MUL_MAXR, sz);
   const bool same = (a == b_);
   const uint64_t* A = a;
   const uint64_t* B = b_;

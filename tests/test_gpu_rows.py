@@ -115,3 +115,39 @@ def test_job_short_rows(log2n, count):
         check("plan")
     finally:
         L.pm_plan_destroy(plan)
+
+
+# transforms of N = 2^16: rows of 2^8 up to 2^22 words, of 2^10 beyond; of 2^17: rows of 2^8
+# below 2^27 words, register blocks alone from there
+@pytest.mark.parametrize("log2n, limbs, polys, row", [(16, 1, 64, 8), (16, 1, 65, 10), (16, 5, 13, 10),
+                                                      (17, 1, 1023, 8), (17, 1, 1024, None), (17, 3, 342, None)])
+def test_il_transforms_of_large_batches(log2n, limbs, polys, row):
+    import torch
+    from paper_2209_01290_amd import lib as L
+    N = 1 << log2n
+    qs = L.pm_ntt_primes(N, limbs, 60)
+    prm = L.Params(N, limbs, primes=qs)
+    fw, iv = oracle_tables(qs, N)
+    x = torch.empty((limbs, polys, N), dtype=torch.int64, device="cuda")
+    for l, q in enumerate(qs):
+        x[l].random_(0, q, generator=torch.Generator(device="cuda").manual_seed(17 + l))
+    ends = [x[:, p].cpu().numpy().astype(np.uint64) for p in (0, polys - 1)]
+    for what, il, rows, one, want in (("fwd", L.pm_ntt_fwd_il, L.pm_ntt_fwd, prm.psi_br, oracle_ntt_fwd),
+                                      ("inv", L.pm_ntt_inv_il, L.pm_ntt_inv, prm.psi_inv_br, oracle_ntt_inv)):
+        L.pm_prof_read(reset=True)
+        L.pm_prof_enable(True)
+        try:
+            y = x.transpose(1, 2).contiguous()
+            il(y, N, limbs, polys, qs, one)
+            torch.cuda.synchronize()
+        finally:
+            L.pm_prof_enable(False)
+        names = L.pm_prof_read(reset=True)
+        assert [n for n in names if "_c" in n] == ([] if row is None else ["il_%s_c%d" % (what, row)]), sorted(names)
+        z = x.clone()
+        rows(z, N, limbs, polys, qs, one)
+        assert torch.equal(y.transpose(1, 2), z)              # every word, against the other layout
+        for p, e in zip((0, polys - 1), ends):
+            got = y[:, :, p].cpu().numpy().astype(np.uint64)
+            msg = first_mismatch(got, want(e[:, None], qs, fw if one is prm.psi_br else iv)[:, 0])
+            assert msg is None, msg

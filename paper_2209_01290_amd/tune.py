@@ -13,11 +13,12 @@ written to a JSON database (the split that is there already stays when it is wit
      "choices": {"polymul": {"16": 12, ...}, ...},
      "timings_ms": {"polymul": {"16": {"12": [0.81, ...], "13": [0.85, ...]}, ...}, ...}}
 
-Small-batch plans (--small): for a single transform or product per call
-(one limb, one polynomial) it times every split with 16 and with 4 words per
+Small-batch plans (--small): for calls of one transform or product and of eight (one
+polynomial under eight moduli) it times every split with 16 and with 4 words per
 thread (device time per call, 20 calls captured in one HIP graph and
-replayed), keeps the fastest per (operation, N) (the plan that is there already when it is
-within 5 %), and finds for each (operation, N >= 2^8) the batch limit (in words) of the
+replayed), keeps the one of least summed relative time per (operation, N) (the plan that
+is there already when it is within 5 %; a choice from single transforms alone took rows of
+2^9 words for 2^16, 1 % ahead there and 14 % behind at four), and finds for each (operation, N >= 2^8) the batch limit (in words) of the
 small-batch plan: over batches of 1, 2, 3, 4, 6, 8, ... polynomials both plans are
 timed, the throughput plan being the database's own, and the limit is the batch up to
 which the small-batch plan gives the least summed time, each batch relative to its better
@@ -208,21 +209,23 @@ def tune_small(log2ns, device="cuda", verbose=True, have=None, choices_now=None)
         if log2n < 5:
             continue
         N = 1 << log2n
-        prm = lib.Params(N, 1, device=dev)
-        a, b = synth.operands(synth.SEED_BASE + 18, prm.q, 1, N)
-        da, db = lib.to_device(a, dev), lib.to_device(b, dev)
-        dc = torch.empty_like(da)
-        x = da.clone()
-        for name, op in OPS.items():
+        for name in OPS:
             lat[name][str(log2n)] = {}
-            for logc, wpt in small_candidates(log2n):
-                lib.pm_tune_set_small(op, log2n, logc, wpt)
-                nbytes = lib.pm_polymul_workspace_bytes(N, 1, 1)
-                ws = torch.empty(max(nbytes // 8, 1), dtype=torch.int64, device=dev)
-                us = _graph_us(torch, _calls(lib, name, prm, N, 1, da, db, dc, x, ws))
-                lat[name][str(log2n)]["%d/%d" % (logc, wpt)] = round(us, 2)
+        for limbs in (1, 8):
+            prm = lib.Params(N, limbs, device=dev)
+            a, b = synth.operands(synth.SEED_BASE + 18, prm.q, 1, N)
+            da, db = lib.to_device(a, dev), lib.to_device(b, dev)
+            dc = torch.empty_like(da)
+            x = da.clone()
+            ws = torch.empty_like(da)
+            for name, op in OPS.items():
+                for logc, wpt in small_candidates(log2n):
+                    lib.pm_tune_set_small(op, log2n, logc, wpt)
+                    us = _graph_us(torch, _calls(lib, name, prm, N, 1, da, db, dc, x, ws, limbs))
+                    lat[name][str(log2n)].setdefault("%d/%d" % (logc, wpt), []).append(round(us, 2))
+        for name, op in OPS.items():
             old = (have or {}).get("choices", {}).get(name, {}).get(str(log2n))
-            best = _pick({k: [v] for k, v in lat[name][str(log2n)].items()}, "%d/%d" % tuple(old) if old else None)
+            best = _pick(lat[name][str(log2n)], "%d/%d" % tuple(old) if old else None)
             best = [int(v) for v in best.split("/")]
             lib.pm_tune_set_small(op, log2n, *best)
             choices[name][str(log2n)] = best

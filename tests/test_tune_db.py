@@ -28,7 +28,8 @@ def test_choices_follow_from_timings(db, op):
 def test_small_plans_follow_from_timings(db, op):
     small = db["small"]
     for n in range(5, 18):
-        t = {k: [v] for k, v in small["latency_us"][op][str(n)].items()}
+        t = small["latency_us"][op][str(n)]
+        assert all(len(v) == 2 for v in t.values())           # one polynomial, eight
         have = "%d/%d" % tuple(small["choices"][op][str(n)])
         assert tune._pick(t, have) == have, (n, have, t)
         if n < tune.LIMIT_MIN_LOG2N:

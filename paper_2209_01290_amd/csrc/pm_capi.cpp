@@ -641,20 +641,49 @@ static int il_plan(unsigned n, int maxlast, int* sizes) {
   }
 }
 
-// Passes of N = 2^n with an LDS row: sizes[0..n-2] register blocks, sizes[n-1]
-// the row. One pass up to 2^10; beyond, the row that measured best (N = 2^11..2^17,
-// batches of 2^22 and 2^25 words): radix-2^4 and 2^5 blocks and rows of 2^8 (four
-// workgroups to a CU) run nearest to the memory's rate. For transforms of 2^16 they are a
-// pass more, 4 + 4 + 8, than rows of 2^10, which pays while the GPU is not full: 2^20, 2^22
-// words 31, 43 us against 40, 45 as 6 + 10; 2^24, 2^28 words 165, 2773 against 144, 2092.
-// (The products' other pass would move three batches more: 6 + 10 + 6 always.)
-static int il_row_plan(unsigned n, bool mul, size_t words, int* sizes) {
-  static const uint8_t rows[2][7] = {{7, 8, 8, 8, 9, 10, 8}, {7, 8, 8, 9, 9, 10, 8}};    // N = 2^11..2^17
-  unsigned row = n <= (unsigned)IL_ROW_MAX ? n : rows[mul][n - IL_ROW_MAX - 1];
-  if (n == 16 && !mul && words <= ((size_t)1 << 22)) row = 8;
+// Passes of N = 2^n with an LDS row of 2^row: sizes[0..n-2] register blocks, sizes[n-1]
+// the row.
+static int il_row_plan(unsigned n, unsigned row, int* sizes) {
   const int np = n > row ? il_plan(n - row, IL_MAXR, sizes) : 0;
   sizes[np] = (int)row;
   return np + 1;
+}
+
+// The rows that measured best, one pass up to 2^10 (N = 2^11..2^17: batches of 2^22 and
+// 2^25 words): radix-2^4 and 2^5 blocks and rows of 2^8 (four workgroups to a CU) run
+// nearest to the memory's rate. Products: 2^16 as 6 + 10 + 6, which moves three batches less
+// than 4 + 4 + 8 + 4 + 4.
+static unsigned il_mul_row(unsigned n) {
+  static const uint8_t rows[7] = {7, 8, 8, 9, 9, 10, 8};
+  return n <= (unsigned)IL_ROW_MAX ? n : rows[n - IL_ROW_MAX - 1];
+}
+
+// Transforms of count = limbs x polys polynomials; 0: register blocks alone. (us: forward,
+// 60 bits.)
+static unsigned il_ntt_row(unsigned n, size_t polys, size_t count) {
+  static const uint8_t rows[7] = {7, 8, 8, 8, 9, 10, 8};
+  const size_t words = count << n;
+  // one block does up to 2^6 (N = 2^6 x 65535: 22.0, as rows 26.0)
+  if (n <= (unsigned)IL_MAXR) return 0;
+  // N = 2^17 is three passes either way, and a row pass touches single lines where a block
+  // touches runs of four: blocks (6 + 6 + 5) once the batch is far beyond the last-level
+  // cache (2^24, 2^26, 2^27, 2^28 words: 160, 692, 1271, 2504 against 153, 682, 1301, 2783)
+  if (n == 17 && words >= ((size_t)1 << 27)) return 0;
+  // an odd count of polynomials puts a row's 16 lanes across two lines: two passes of blocks
+  // are faster where the GPU is full, up to 2^9 while the batch stays in the cache (2^7, 2^8,
+  // 2^9 x 8191: 12, 18, 28 against 15, 22, 30, x 40001 32, 58, 112 against 30, 53, 106;
+  // 2^10 x 3001, x 8191, x 20350 31, 50, 116 against 28, 56, 126; 2^12 x 999, x 3001, x 8191
+  // 49, 82, 205 against 41, 95, 236)
+  if (polys % 16 && n <= 12 && count >= (n <= 10 ? 4096u : 2048u) && (n >= 10 || words <= ((size_t)1 << 22))) return 0;
+  // a part-empty GPU takes shorter rows, more workgroups of them (2^10 x 101: 2 + 8 stages 12,
+  // one row 18; 2^14 x 32: 4 + 3 + 7 20, 6 + 8 25; 2^15 x 32: 4 + 3 + 8 26, 6 + 9 30; 2^16 x
+  // 16, x 64: 4 + 4 + 8 31, 43, 6 + 10 40, 45)
+  if (n == 10 && words <= ((size_t)1 << 19)) return 8;
+  if (n == 14 && words <= ((size_t)1 << 20)) return 7;
+  if (n == 15 && words < ((size_t)1 << 22)) return 8;
+  if (n == 16 && words <= ((size_t)1 << 22)) return 8;
+  // (2^16 beyond: 6 + 10; 2^24, 2^28 words 144, 2092, as 4 + 4 + 8 165, 2773)
+  return n <= (unsigned)IL_ROW_MAX ? n : rows[n - IL_ROW_MAX - 1];
 }
 
 static const char* il_name(int mode, int logr) {
@@ -689,15 +718,9 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   if ((rc = check_batch(&b, N, limbs, polys, q))) return rc;
   if ((rc = check_ptr(x, "x")) || (rc = check_ptr(tw, inv ? "psi_inv_br" : "psi_br"))) return rc;
   int sz[32];
-  // the last pass (the first one back) is an LDS row, which scales by 1/N; one register
-  // block does up to 2^6 (N = 2^6 x 65535: 22.0 us, as rows 26.0). N = 2^17 is three passes
-  // either way, and a row pass touches single lines where a block touches runs of four: from
-  // the size where the batch is far beyond the last-level cache, blocks alone (6 + 6 + 5) are
-  // the faster form (2^24, 2^26, 2^27, 2^28 words: 160, 692, 1271, 2504 us against 153, 682,
-  // 1301, 2783).
-  const size_t words = N * limbs * polys;
-  const bool row = b.log2n > (unsigned)IL_MAXR && !(b.log2n == PM_MAX_LOG2N && words >= IL_BLOCK_WORDS);
-  const int np = row ? il_row_plan(b.log2n, false, words, sz) : il_plan(b.log2n, IL_MAXR, sz);
+  // the last pass (the first one back) is an LDS row, which scales by 1/N, if there is one
+  const unsigned row = il_ntt_row(b.log2n, polys, limbs * polys);
+  const int np = row ? il_row_plan(b.log2n, row, sz) : il_plan(b.log2n, IL_MAXR, sz);
   hipStream_t s = (hipStream_t)stream;
   if (validate_enabled() &&
       (rc = validate_batch<uint64_t>(b, {{x, "x"}}, {{tw, inv ? "psi_inv_br" : "psi_br"}}, s)))
@@ -705,7 +728,7 @@ static int ntt_common_il(uint64_t* x, size_t N, size_t limbs, size_t polys, cons
   rc = for_chunks(b, [&](size_t l0, size_t nl, const LimbSet& ls) -> hipError_t {
     uint64_t* xs = x + l0 * polys * N;
     const uint64_t* t = tw + l0 * N;
-    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls, !row};
+    IlArgs a{xs, nullptr, xs, nullptr, t, t, b.log2n, 0, (uint32_t)polys, (uint32_t)nl, 1, &ls, row == 0};
     const auto run = [&](int k, int mode) {
       return row && k == np - 1 ? run_il_row(sz[k], b.kind, mode, a, s) : run_il(sz[k], b.kind, mode, a, s);
     };
@@ -758,7 +781,7 @@ int pm_polymul_il(const uint64_t* a, const uint64_t* b_, uint64_t* c, size_t N, 
   int sz[32];
   const bool needs_ws = il_plan(b.log2n, IL_MUL_MAXR, sz) > 1;
   const bool row = b.log2n >= (unsigned)IL_ROW_MIN;
-  const int np = row ? il_row_plan(b.log2n, true, N * limbs * polys, sz) : il_plan(b.log2n, IL_MUL_MAXR, sz);
+  const int np = row ? il_row_plan(b.log2n, il_mul_row(b.log2n), sz) : il_plan(b.log2n, IL_MUL_MAXR, sz);
   const bool same = (a == b_);
   const uint64_t* A = a;
   const uint64_t* B = b_;

@@ -103,7 +103,6 @@ hipError_t launch_il(int logr, int kind, int mode, const IlArgs& a, hipStream_t 
 // The last logc stages in LDS rows of 2^logc coefficients (il_rows.hip): IL_FWD, IL_INV
 // (scaled by 1/N) A -> C, IL_MUL (the product's middle) A, B -> C.
 constexpr int IL_ROW_MIN = 6, IL_ROW_MAX = 10;
-constexpr size_t IL_BLOCK_WORDS = (size_t)1 << 27;   // transforms of N = 2^17: no rows from this batch on
 hipError_t launch_il_row(int logc, int kind, int mode, const IlArgs& a, hipStream_t s);
 
 // PM_VALIDATE scan (pm_validate.hip): flags_dev[l] = 1 if some word of limb

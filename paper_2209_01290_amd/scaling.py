@@ -67,6 +67,18 @@ def _graph_us(torch, fn, calls=20, reps=10):
     return per[len(per) // 2]
 
 
+def _passes(torch, lib, fn):
+    """Launches of one call, from the library's event timer: each reads and writes the batch once."""
+    lib.pm_prof_read(reset=True)
+    lib.pm_prof_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+    finally:
+        lib.pm_prof_enable(False)
+    return sum(v[0] for v in lib.pm_prof_read(reset=True).values())
+
+
 def batch_scaling(torch, lib, log2n=16, max_log2p=15, verbose=True):
     from . import synth
     dev = torch.device("cuda")
@@ -81,16 +93,12 @@ def batch_scaling(torch, lib, log2n=16, max_log2p=15, verbose=True):
             synth.uniform_mod_device([synth.key(SEED, lp, c)], chunk, prm.q, x[c * chunk:(c + 1) * chunk].view(1, chunk))
         reps = max(5, min(200, (1 << 22) // (P * N // 64 + 1)))
         row = {"N": N, "polys": P, "bytes": P * N * 8}
-        # HBM bytes each layout moves per call: every pass reads and writes the batch once
-        std_passes = 2 if lib.pm_tune_get(lib.OP_NTT_FWD, log2n) < log2n else 1
-        il_passes = -(-log2n // 6)            # blocks of at most 6 stages
-        moved = {"standard": std_passes * 16 * N * P, "interleaved": il_passes * 16 * N * P}
         for name, fn in (("standard", lambda: lib.pm_ntt_fwd(x, N, 1, P, prm.q, prm.psi_br)),
                          ("interleaved", lambda: lib.pm_ntt_fwd_il(x, N, 1, P, prm.q, prm.psi_br))):
             us = _median_us(torch, fn, reps)
             row[name + "_us_per_call"] = round(us, 2)
             row[name + "_us_per_ntt"] = round(us / P, 4)
-            row[name + "_GBps"] = round(moved[name] / us / 1e3, 1)
+            row[name + "_GBps"] = round(_passes(torch, lib, fn) * 16 * N * P / us / 1e3, 1)
         rows.append(row)
         if verbose:
             print(json.dumps(row), flush=True)
